@@ -59,10 +59,12 @@ enum {
 enum {
     LSP_FORM_FP64 = 0,  /* reference form: FP64 phases, FP64 library sin/cos per
                            term, FP64 sums (the method exactly as Section 2 states it) */
-    LSP_FORM_FP32P = 1  /* FP32 sums and trig, phases reduced in FP64; sin/cos seeded
-                           by the hardware per observation and advanced across a lane's
-                           frequencies by angle addition; ill-conditioned bins
-                           recomputed in FP64                                         */
+    LSP_FORM_FP32P = 1  /* FP32 sums and trig, phases reduced in FP64, hardware
+                           sin/cos, the bins reached from them by angle addition:
+                           on the matrix cores (each factor as two f16 halves, 22
+                           significant bits, FP32 accumulators) where the library
+                           chooses the launch, else along a lane's frequencies on
+                           the vector units; ill-conditioned bins recomputed in FP64   */
 };
 
 /* Frequency unit of the grid. */
@@ -153,7 +155,10 @@ typedef struct {
  * Options.  A zero-initialised struct means: FP64 form, unnormalised P_LS, y
  * used as given, FP32 periodogram, library-chosen tuning; callers normally
  * start from lsp_default_options().  Tuning fields left at 0 are chosen by the
- * library (built-in heuristics for the shape).
+ * library (built-in heuristics for the shape).  The standard FP32 form runs the
+ * matrix-core kernels when k_per_lane, waves_per_wg, t_split, schedule,
+ * recurrence, wave_split, obs_read and seed_trig are all 0; a value in any of
+ * them describes, and selects, the vector kernels.
  */
 typedef struct {
     int32_t form;          /* LSP_FORM_*                                               */
@@ -420,7 +425,9 @@ lsp_status lsp_plan_launch(lsp_plan plan, void *stream);
 void lsp_plan_destroy(lsp_plan plan);
 
 /*
- * Launch-shape autotuner for the FP32 form.  Times candidate shapes (K
+ * Launch-shape autotuner for the FP32 form's vector kernels (the matrix-core
+ * kernels, which run when every tuning field is 0, need no tuning and are the
+ * faster choice on the sizes measured).  Times candidate shapes (K
  * frequencies per lane, wavefronts per workgroup, recurrence, schedule and,
  * for one object, the observation split) on the caller's data -- for a batch,
  * on a prefix of its objects holding about 1e11 evaluations -- and writes the
@@ -686,9 +693,12 @@ lsp_status lsp_select_fallback(const lsp_peak *peaks, const float *mass, int64_t
  * these options: the tuning fields of `opt` left at 0 filled with the
  * library's choices, the bins one frequency tile covers, the consecutive
  * tiles one work item takes and the number of work items.  It is what the
- * call would enqueue; nothing is launched.  Used to state the K, recurrence
- * and schedule behind a measurement (the work per bin of Section 2 depends
- * on them).
+ * call would enqueue on the vector kernels; nothing is launched.  Used to
+ * state the K, recurrence and schedule behind a measurement (the work per bin
+ * of Section 2 depends on them).  A standard FP32 call with every tuning field
+ * at 0 runs the matrix-core kernels instead (see lsp_options), whose shape has
+ * no such choices; the shape reported is the one its vector kernels would
+ * take.
  *   resolved : host, receives the options with every AUTO / 0 field resolved
  *              (form, normalize, subtract_mean and pgram_dtype as given).
  *   tile_freqs, tiles_per_item, n_items : host, may be NULL.

@@ -48,7 +48,11 @@ struct Config {
     int64_t n_obs;
     bool keys;              // FP32 form, unsplit: per-group peak keys + tile flag bits
     bool lpt;               // rows handed out longest first (lsp_order.hip)
+    int mx;                 // matrix-core sums: kMxOff, kMxTiles or kMxSplit
+    int mx_waves;           // kMxTiles: waves (2,048-bin tiles) per workgroup
 };
+
+enum { kMxOff = 0, kMxTiles = 1, kMxSplit = 2 };
 
 // Rows of work.  The whole-grid entry points use one row per object covering
 // every bin; lsp_batch_rows names (object, band) rows and groups of rows that
@@ -107,12 +111,14 @@ lsp_status valid_options(const lsp_options* o) {
 
 // Launch configuration: a pure function of the shape and the options, so that
 // lsp_workspace_bytes and the call agree.
-lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* o,
-                   const Rows& rows, Config* c, const Method& method = Method{}) {
+lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* o,
+                          const Rows& rows, Config* c, const Method& method) {
     // Launch shapes are sized for the bins of one row.
     const int64_t n_f = rows.row_band ? (rows.band_bins < g->n_f ? rows.band_bins : g->n_f) : g->n_f;
     const bool whole = rows.whole;
     c->gen = method.gen;
+    c->mx = kMxOff;
+    c->mx_waves = 0;
     c->obs = o->obs_read == LSP_OBS_DIRECT ? LSP_OBS_DIRECT : LSP_OBS_LDS;
     c->trig = o->seed_trig == LSP_TRIG_AUTO ? LSP_TRIG_HW : o->seed_trig;
     // The read-path and seed-trig variants exist for the standard FP32 form
@@ -282,6 +288,39 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
         rows.n_rows > 1 && rows.n_rows <= (int64_t)INT32_MAX && n_obj > 1 && c->split == 1;
     const double terms = (double)n_obs * (double)n_f * ((double)rows.n_rows / (double)n_obj);
     c->lpt = orderable && (o->order == LSP_ORDER_LPT || (o->order == LSP_ORDER_AUTO && terms >= 1e10));
+    return LSP_OK;
+}
+
+// The launch configuration of a call: the vector kernels' shape, or, where
+// every tuning field is left to the library, the matrix-core kernels'
+// (lsp_mx.hip) with 1,024-bin fix-up tiles.
+lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* o,
+                   const Rows& rows, Config* c, const Method& method = Method{}) {
+    const lsp_status st = resolve_vector(n_obj, n_obs, g, o, rows, c, method);
+    if (st != LSP_OK) return st;
+    const bool left = !o->k_per_lane && !o->waves_per_wg && !o->t_split &&
+                      o->schedule == LSP_SCHED_AUTO && o->recurrence == LSP_REC_AUTO &&
+                      o->wave_split == LSP_WSPLIT_AUTO && o->obs_read == LSP_OBS_AUTO &&
+                      o->seed_trig == LSP_TRIG_AUTO;
+    if (o->form != LSP_FORM_FP32P || method.gen || !left) return LSP_OK;
+    if (g->n_f > (int64_t)0xFFFFFFFE) return LSP_OK;
+    const int64_t n_f = rows.row_band ? (rows.band_bins < g->n_f ? rows.band_bins : g->n_f) : g->n_f;
+    const bool one_row = rows.whole && n_obj == 1;
+    const int waves = n_f > 4096 ? 4 : 2;
+    const int64_t bins = mx_item_bins(waves, one_row);
+    const int64_t tiles = (n_f + kMxTile - 1) / kMxTile;
+    if (tiles * rows.rows_per_group > kMaxGrid / rows.n_rows) return LSP_OK;
+    c->mx = one_row ? kMxSplit : kMxTiles;
+    c->mx_waves = waves;
+    c->split = 1;
+    c->persistent = 0;
+    c->tile_freqs = kMxTile;
+    c->tiles_per_row = tiles;
+    c->tiles_per_item = bins / kMxTile;
+    c->chunks_per_row = (n_f + bins - 1) / bins;
+    c->n_items = rows.n_rows * c->chunks_per_row;
+    c->rec_per_group = tiles * rows.rows_per_group;
+    c->keys = true;
     return LSP_OK;
 }
 
@@ -462,6 +501,8 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
         if ((f32 ? launch_gen_fp32p(mp, c.k, c.waves, s) : launch_gen_fp64(mp, c.k, c.waves, s)) !=
             hipSuccess)
             return LSP_EHIP;
+    } else if (c.mx != kMxOff) {
+        if (launch_mx(mp, c.mx_waves, c.mx == kMxSplit, s) != hipSuccess) return LSP_EHIP;
     } else if (f32) {
         if (launch_fp32p(mp, c.k, c.waves, c.rec, s, c.obs, c.trig) != hipSuccess)
             return LSP_EHIP;
@@ -867,7 +908,7 @@ lsp_status lsp_describe_launch(int64_t n_obj, int64_t n_obs, const lsp_grid* gri
     lsp::Method method;
     method.gen = generalized != 0;
     lsp::Config c;
-    st = lsp::resolve(n_obj, n_obs, grid, &opt, lsp::whole_grid(n_obj, grid), &c, method);
+    st = lsp::resolve_vector(n_obj, n_obs, grid, &opt, lsp::whole_grid(n_obj, grid), &c, method);
     if (st != LSP_OK) return st;
     lsp_options r = opt;
     r.k_per_lane = c.k;

@@ -68,6 +68,18 @@ __device__ double block_sum(double v, double* sh) {
     return out;
 }
 
+__device__ double block_max(double v, double* sh) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+    const int wave = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) sh[wave] = v;
+    __syncthreads();
+    double out = sh[0];
+    for (int w = 1; w < kPrepThreads / kWave; ++w) out = fmax(out, sh[w]);
+    __syncthreads();
+    return out;
+}
+
 __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) {
     __shared__ Red sh_red[kPrepThreads / kWave];
     __shared__ double sh_sum[kPrepThreads / kWave];
@@ -118,13 +130,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
                               : ((P.subtract_mean && n > 0) ? r.sy / (double)n : 0.0);
     const double t0 = (n > 0 && !r.bad) ? 0.5 * (r.tmin + r.tmax) : 0.0;
 
-    double sq = 0.0;
+    double sq = 0.0, big = 0.0;
     for (int64_t j = j0 + tid; j < j1; j += kPrepThreads) {
         const double yc = P.y[j] - ybar;
         const double w = P.gen ? gen_weight(P.dy, j, wnorm) : 1.0;
         sq += w * yc * yc;
+        big = fmax(big, fabs(yc));
     }
     const double syy = block_sum(sq, sh_sum);
+    big = block_max(big, sh_sum);
 
     if (tid == 0) {
         ObjMeta m = {};
@@ -134,6 +148,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
         m.syy = syy;
         m.t0 = t0;
         m.wnorm = wnorm;
+        m.exps = mx_scale_exp(big) & 0xffff;
         int32_t st = LSP_OBJ_OK;
         if (r.bad || (P.gen && n > 0 && !ok_w))
             st = LSP_OBJ_NONFINITE;
