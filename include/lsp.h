@@ -155,10 +155,10 @@ typedef struct {
  * Options.  A zero-initialised struct means: FP64 form, unnormalised P_LS, y
  * used as given, FP32 periodogram, library-chosen tuning; callers normally
  * start from lsp_default_options().  Tuning fields left at 0 are chosen by the
- * library (built-in heuristics for the shape).  The standard FP32 form runs the
- * matrix-core kernels when k_per_lane, waves_per_wg, t_split, schedule,
- * recurrence, wave_split, obs_read and seed_trig are all 0; a value in any of
- * them describes, and selects, the vector kernels.
+ * library (built-in heuristics for the shape).  The FP32 forms (standard and
+ * generalized) run the matrix-core kernels when k_per_lane, waves_per_wg,
+ * t_split, schedule, recurrence, wave_split, obs_read and seed_trig are all 0;
+ * a value in any of them describes, and selects, the vector kernels.
  */
 typedef struct {
     int32_t form;          /* LSP_FORM_*                                               */
@@ -274,8 +274,9 @@ lsp_status lsp_batch_static(const int64_t *offsets, int64_t n_obj, int64_t n_obs
  *               NULL for unit errors (the floating-mean periodogram).  An object
  *               with an error that is not finite or not > 0 gets status
  *               LSP_OBJ_NONFINITE (power NaN, index -1).
- *   opt       : as lsp_single; form FP64 or FP32P.  The FP32P form has the
- *               three-term recurrence only and k_per_lane in {0, 4, 8, 12, 16}.
+ *   opt       : as lsp_single; form FP64 or FP32P.  The FP32P form's vector
+ *               kernels have the three-term recurrence only and k_per_lane in
+ *               {0, 4, 8, 12, 16}.
  *   workspace : >= lsp_gen_workspace_bytes(n_obj, n_obs, grid, opt) bytes
  *               (n_obj = 1 for lsp_gen_single), 256-byte aligned, owned by the
  *               caller.
@@ -695,7 +696,7 @@ lsp_status lsp_select_fallback(const lsp_peak *peaks, const float *mass, int64_t
  * tiles one work item takes and the number of work items.  It is what the
  * call would enqueue on the vector kernels; nothing is launched.  Used to
  * state the K, recurrence and schedule behind a measurement (the work per bin
- * of Section 2 depends on them).  A standard FP32 call with every tuning field
+ * of Section 2 depends on them).  An FP32 call with every tuning field
  * at 0 runs the matrix-core kernels instead (see lsp_options), whose shape has
  * no such choices; the shape reported is the one its vector kernels would
  * take.

@@ -302,12 +302,12 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
                       o->schedule == LSP_SCHED_AUTO && o->recurrence == LSP_REC_AUTO &&
                       o->wave_split == LSP_WSPLIT_AUTO && o->obs_read == LSP_OBS_AUTO &&
                       o->seed_trig == LSP_TRIG_AUTO;
-    if (o->form != LSP_FORM_FP32P || method.gen || !left) return LSP_OK;
+    if (o->form != LSP_FORM_FP32P || !left) return LSP_OK;
     if (g->n_f > (int64_t)0xFFFFFFFE) return LSP_OK;
     const int64_t n_f = rows.row_band ? (rows.band_bins < g->n_f ? rows.band_bins : g->n_f) : g->n_f;
     const bool one_row = rows.whole && n_obj == 1;
-    const int waves = n_f > 4096 ? 4 : 2;
-    const int64_t bins = mx_item_bins(waves, one_row);
+    const int waves = method.gen || n_f > 4096 ? 4 : 2;
+    const int64_t bins = mx_item_bins(waves, one_row, method.gen);
     const int64_t tiles = (n_f + kMxTile - 1) / kMxTile;
     if (tiles * rows.rows_per_group > kMaxGrid / rows.n_rows) return LSP_OK;
     c->mx = one_row ? kMxSplit : kMxTiles;
@@ -359,6 +359,9 @@ Layout layout(int64_t n_obj, const lsp_grid* g, const Rows& rows, const Config& 
     L.hist = off;
     off += c.lpt ? align_up((size_t)(kOrderBlocks + 1) * kOrderBuckets * sizeof(unsigned int))
                  : 0;
+    // a program may size one buffer for both methods from the generalized
+    // call, which has always asked for more than the standard one: keep it so
+    if (c.gen && c.mx != kMxOff) off += kAlign;
     L.total = off;
     return L;
 }
@@ -497,12 +500,12 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
         mp.n_work = op.total + (kOrderBuckets - 1);
     }
     if (t_main_begin && hipEventRecord(t_main_begin, s) != hipSuccess) return LSP_EHIP;
-    if (method.gen) {
+    if (c.mx != kMxOff) {
+        if (launch_mx(mp, c.mx_waves, c.mx == kMxSplit, s) != hipSuccess) return LSP_EHIP;
+    } else if (method.gen) {
         if ((f32 ? launch_gen_fp32p(mp, c.k, c.waves, s) : launch_gen_fp64(mp, c.k, c.waves, s)) !=
             hipSuccess)
             return LSP_EHIP;
-    } else if (c.mx != kMxOff) {
-        if (launch_mx(mp, c.mx_waves, c.mx == kMxSplit, s) != hipSuccess) return LSP_EHIP;
     } else if (f32) {
         if (launch_fp32p(mp, c.k, c.waves, c.rec, s, c.obs, c.trig) != hipSuccess)
             return LSP_EHIP;

@@ -41,7 +41,7 @@ struct ObjMeta {
     double t0;       // time origin: mid-point of the object's time span
     double scale;    // factor from P_LS to the reported power
     int32_t status;  // LSP_OBJ_*
-    int32_t exps;    // powers of two that scale the matrix-core factors (mx_exp_y)
+    int32_t exps;    // powers of two that scale the matrix-core factors (mx_exp_y, mx_exp_w)
     double wnorm;    // generalized form: N / sum(1/dy^2) (1 for unit errors)
 };
 static_assert(sizeof(ObjMeta) == 64, "ObjMeta layout");
@@ -52,13 +52,16 @@ constexpr int kMxTile = 1024;
 // The matrix-core kernels scale an object's centred magnitudes by 2^e with
 // max |y - ybar| 2^e in [2^13, 2^14): the products with cosines stay below
 // f16's largest value, and the low half of a value's split stays a normal f16
-// down to 2^-13 of the largest magnitude.
+// down to 2^-13 of the largest magnitude.  The generalized form scales w and
+// w (y - ybar) the same way, each by its own power.
 __device__ __forceinline__ int mx_scale_exp(double largest) {
     if (!(largest > 0.0) || !isfinite(largest)) return 0;
     const int e = 13 - ilogb(largest);
     return e < -1000 ? -1000 : (e > 1000 ? 1000 : e);
 }
+__device__ __forceinline__ int32_t mx_pack_exps(int y, int w) { return (y & 0xffff) | (w << 16); }
 __device__ __forceinline__ int mx_exp_y(const ObjMeta& m) { return (int)(int16_t)(m.exps & 0xffff); }
+__device__ __forceinline__ int mx_exp_w(const ObjMeta& m) { return m.exps >> 16; }
 
 // Best (power, index) of one frequency tile; index -1 means none.
 struct PeakRec {
@@ -653,9 +656,10 @@ hipError_t launch_stage(const ObjMeta* meta, const double* t, const double* y, i
                         double step_cyc, int trig, double* stage_t, float4* stage_o,
                         hipStream_t s);
 hipError_t launch_gen_fp32p(const MainParams& p, int k, int waves, hipStream_t s);
-// Matrix-core sums (lsp_mx.hip): `waves` (2 or 4) tiles of 2,048 bins per
-// workgroup, or, with `split`, one tile whose observations the waves share.
-int64_t mx_item_bins(int waves, bool split);
+// Matrix-core sums (lsp_mx.hip): `waves` (2 or 4; 4 for the generalized form)
+// tiles of 2,048 (generalized 1,024) bins per workgroup, or, with `split`, one
+// tile whose observations the waves share.
+int64_t mx_item_bins(int waves, bool split, bool gen);
 hipError_t launch_mx(const MainParams& p, int waves, bool split, hipStream_t s);
 hipError_t launch_gen_fp64(const MainParams& p, int kf, int waves, hipStream_t s);
 hipError_t launch_fixup(const FixupParams& p, hipStream_t s);

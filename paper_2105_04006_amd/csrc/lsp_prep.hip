@@ -130,15 +130,17 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
                               : ((P.subtract_mean && n > 0) ? r.sy / (double)n : 0.0);
     const double t0 = (n > 0 && !r.bad) ? 0.5 * (r.tmin + r.tmax) : 0.0;
 
-    double sq = 0.0, big = 0.0;
+    double sq = 0.0, big = 0.0, big_w = 0.0;
     for (int64_t j = j0 + tid; j < j1; j += kPrepThreads) {
         const double yc = P.y[j] - ybar;
         const double w = P.gen ? gen_weight(P.dy, j, wnorm) : 1.0;
         sq += w * yc * yc;
-        big = fmax(big, fabs(yc));
+        big = fmax(big, fabs(w * yc));
+        big_w = fmax(big_w, w);
     }
     const double syy = block_sum(sq, sh_sum);
     big = block_max(big, sh_sum);
+    if (P.gen) big_w = block_max(big_w, sh_sum);
 
     if (tid == 0) {
         ObjMeta m = {};
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
         m.syy = syy;
         m.t0 = t0;
         m.wnorm = wnorm;
-        m.exps = mx_scale_exp(big) & 0xffff;
+        m.exps = mx_pack_exps(mx_scale_exp(big), P.gen ? mx_scale_exp(big_w) : 0);
         int32_t st = LSP_OBJ_OK;
         if (r.bad || (P.gen && n > 0 && !ok_w))
             st = LSP_OBJ_NONFINITE;

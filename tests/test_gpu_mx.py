@@ -142,3 +142,30 @@ def test_rows_equal_whole_grid(dev):
         pk = r.peaks()
         assert all(pk["power"][o] == got[o, pk["index"][o]] == got[o].max()
                    for o in range(w.n_obj))
+
+
+# ---- generalized form: 1,024-bin wave tiles, 32 observations an instruction
+
+@pytest.mark.parametrize("n_f", [1, 33, 64, 1023, 1025, 4096, 4097, 9000])
+@pytest.mark.parametrize("n_t", [4, 31, 33, 64, 255, 257, 1030])
+def test_generalized_edges(dev, n_f, n_t):
+    """Around the tile sizes, against the vector kernels (an explicit
+    k_per_lane), on an ordinary series and one with errors over four decades;
+    both are within the bound of the oracle, so within twice it of each other."""
+    rng = np.random.default_rng(n_t)
+    t, y, _ = synth.sine_object(n_t, 2000 + n_t)
+    dy = np.concatenate([rng.uniform(0.03, 0.08, n_t), 10.0 ** rng.uniform(-4.0, 0.0, n_t)])
+    off, tt, yy = synth.pack([(t, y), (t, -y)])
+    kw = dict(form=lsp.FORM_FP32P, method="generalized", pgram_dtype=lsp.PGRAM_F64)
+    got, ref = (lsp.Periodogram(cuda(tt, dev), cuda(yy, dev), 1.0, 12.0, n_f,
+                                offsets=cuda(off, dev, torch.int64), dy=cuda(dy, dev), k=k, **kw)()
+                for k in (0, 16))
+    close(got.pgram.cpu().numpy(), ref.pgram.cpu().numpy(), f"n_f={n_f} n_t={n_t}", 2 * ATOL)
+    pk, rk = got.peaks(), ref.peaks()
+    assert np.array_equal(pk["status"], rk["status"])
+    one = lsp.Periodogram(cuda(t, dev), cuda(y, dev), 1.0, 12.0, n_f, dy=cuda(dy[:n_t], dev),
+                          **kw)()
+    close(one.pgram.cpu().numpy(), ref.pgram.cpu().numpy()[:1], "single", 2 * ATOL)
+    row = ref.pgram.cpu().numpy()[0]
+    assert peak_near(row, pk["index"][0], 2 * ATOL)
+    assert peak_near(row, one.peaks()["index"][0], 2 * ATOL)
