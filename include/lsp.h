@@ -57,8 +57,10 @@ enum {
 
 /* Arithmetic form of the hot loop. */
 enum {
-    LSP_FORM_FP64 = 0,  /* reference form: FP64 phases, FP64 library sin/cos per
-                           term, FP64 sums (the method exactly as Section 2 states it) */
+    LSP_FORM_FP64 = 0,  /* reference form: FP64 phases reduced exactly, FP64 sin/cos
+                           and sums: by angle addition on the FP64 matrix cores where
+                           the library chooses the launch, else with a library
+                           sin/cos per term (the method as Section 2 states it)       */
     LSP_FORM_FP32P = 1  /* FP32 sums and trig, phases reduced in FP64, hardware
                            sin/cos, the bins reached from them by angle addition:
                            on the matrix cores (each factor as two f16 halves, 22
@@ -155,8 +157,8 @@ typedef struct {
  * Options.  A zero-initialised struct means: FP64 form, unnormalised P_LS, y
  * used as given, FP32 periodogram, library-chosen tuning; callers normally
  * start from lsp_default_options().  Tuning fields left at 0 are chosen by the
- * library (built-in heuristics for the shape).  The FP32 forms (standard and
- * generalized) run the matrix-core kernels when k_per_lane, waves_per_wg,
+ * library (built-in heuristics for the shape).  Every form (standard and
+ * generalized) runs its matrix-core kernels when k_per_lane, waves_per_wg,
  * t_split, schedule, recurrence, wave_split, obs_read and seed_trig are all 0;
  * a value in any of them describes, and selects, the vector kernels.
  */
@@ -696,10 +698,9 @@ lsp_status lsp_select_fallback(const lsp_peak *peaks, const float *mass, int64_t
  * tiles one work item takes and the number of work items.  It is what the
  * call would enqueue on the vector kernels; nothing is launched.  Used to
  * state the K, recurrence and schedule behind a measurement (the work per bin
- * of Section 2 depends on them).  An FP32 call with every tuning field
- * at 0 runs the matrix-core kernels instead (see lsp_options), whose shape has
- * no such choices; the shape reported is the one its vector kernels would
- * take.
+ * of Section 2 depends on them).  A call with every tuning field at 0 runs the
+ * matrix-core kernels instead (see lsp_options), whose shape has no such
+ * choices; the shape reported is the one its vector kernels would take.
  *   resolved : host, receives the options with every AUTO / 0 field resolved
  *              (form, normalize, subtract_mean and pgram_dtype as given).
  *   tile_freqs, tiles_per_item, n_items : host, may be NULL.

@@ -64,10 +64,11 @@ struct Rows {
     int64_t band_bins;        // bins per band (n_f when row_band is NULL)
     int32_t rows_per_group;
     bool whole;               // lsp_single / lsp_batch: one whole-grid row per object
+    int64_t n_batch;          // objects of the batch this call is, or is a part of
 };
 
 Rows whole_grid(int64_t n_obj, const lsp_grid* g) {
-    return Rows{nullptr, nullptr, n_obj, g ? g->n_f : 0, 1, true};
+    return Rows{nullptr, nullptr, n_obj, g ? g->n_f : 0, 1, true, n_obj};
 }
 
 struct Layout {
@@ -293,7 +294,7 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
 
 // The launch configuration of a call: the vector kernels' shape, or, where
 // every tuning field is left to the library, the matrix-core kernels'
-// (lsp_mx.hip) with 1,024-bin fix-up tiles.
+// (lsp_mx.hip with 1,024-bin fix-up tiles; lsp_fx.hip with 512-bin records).
 lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* o,
                    const Rows& rows, Config* c, const Method& method = Method{}) {
     const lsp_status st = resolve_vector(n_obj, n_obs, g, o, rows, c, method);
@@ -302,25 +303,44 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
                       o->schedule == LSP_SCHED_AUTO && o->recurrence == LSP_REC_AUTO &&
                       o->wave_split == LSP_WSPLIT_AUTO && o->obs_read == LSP_OBS_AUTO &&
                       o->seed_trig == LSP_TRIG_AUTO;
-    if (o->form != LSP_FORM_FP32P || !left) return LSP_OK;
-    if (g->n_f > (int64_t)0xFFFFFFFE) return LSP_OK;
+    if (!left) return LSP_OK;
+    const bool f32 = o->form == LSP_FORM_FP32P;
+    if (f32 && g->n_f > (int64_t)0xFFFFFFFE) return LSP_OK;
     const int64_t n_f = rows.row_band ? (rows.band_bins < g->n_f ? rows.band_bins : g->n_f) : g->n_f;
-    const bool one_row = rows.whole && n_obj == 1;
-    const int waves = method.gen || n_f > 4096 ? 4 : 2;
-    const int64_t bins = mx_item_bins(waves, one_row, method.gen);
-    const int64_t tiles = (n_f + kMxTile - 1) / kMxTile;
+    // One tile per wave, or, where the batch has too few tiles to fill the
+    // chip's 2,048 wave slots, the waves of a workgroup share a tile and split
+    // its observations.  Measured (us, own tile / shared; FP32): 200 tiles of
+    // 500 points 45 / 26, of 100 points 24 / 21; 500 tiles 48 / 40 and (60
+    // points) 22 / 26; 1,000 tiles of 200 points 39 / 49, of 1,000 points
+    // 108 / 93; one series of 4,096 points, 1,954 tiles, 463 / 575.  FP64: 400
+    // tiles of 500 points 85 / 60; 2,000 tiles of 300 points 99 / 111.  The
+    // count is that of the whole batch, so that parts of it (row mode, the
+    // host-return chunks) add their sums in the same order.
+    const int64_t wave_bins = !f32 ? kFxTile : method.gen ? kMxTile : 2 * kMxTile;
+    const int64_t count = rows.n_batch * rows.rows_per_group * ((n_f + wave_bins - 1) / wave_bins);
+    const bool split = count <= (f32 && rows.n_batch > 1 ? 400 : 1024);
+    int waves;
+    if (!f32)
+        waves = split && count <= 512 ? 8 : 4;
+    else if (split)
+        waves = 8;
+    else
+        waves = method.gen || n_f > 2 * wave_bins ? 4 : (n_f > wave_bins ? 2 : 1);
+    const int64_t bins = f32 ? mx_item_bins(waves, split, method.gen) : fx_item_bins(waves, split);
+    const int64_t tile = f32 ? kMxTile : kFxTile;
+    const int64_t tiles = (n_f + tile - 1) / tile;
     if (tiles * rows.rows_per_group > kMaxGrid / rows.n_rows) return LSP_OK;
-    c->mx = one_row ? kMxSplit : kMxTiles;
+    c->mx = split ? kMxSplit : kMxTiles;
     c->mx_waves = waves;
     c->split = 1;
     c->persistent = 0;
-    c->tile_freqs = kMxTile;
+    c->tile_freqs = tile;
     c->tiles_per_row = tiles;
-    c->tiles_per_item = bins / kMxTile;
+    c->tiles_per_item = bins / tile;
     c->chunks_per_row = (n_f + bins - 1) / bins;
     c->n_items = rows.n_rows * c->chunks_per_row;
     c->rec_per_group = tiles * rows.rows_per_group;
-    c->keys = true;
+    c->keys = f32;
     return LSP_OK;
 }
 
@@ -501,7 +521,9 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
     }
     if (t_main_begin && hipEventRecord(t_main_begin, s) != hipSuccess) return LSP_EHIP;
     if (c.mx != kMxOff) {
-        if (launch_mx(mp, c.mx_waves, c.mx == kMxSplit, s) != hipSuccess) return LSP_EHIP;
+        const bool split = c.mx == kMxSplit;
+        if ((f32 ? launch_mx(mp, c.mx_waves, split, s) : launch_fx(mp, c.mx_waves, split, s)) != hipSuccess)
+            return LSP_EHIP;
     } else if (method.gen) {
         if ((f32 ? launch_gen_fp32p(mp, c.k, c.waves, s) : launch_gen_fp64(mp, c.k, c.waves, s)) !=
             hipSuccess)
@@ -585,21 +607,22 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
 }  // namespace
 
 // Whole-grid batch call and its workspace size, for the host-return pipeline.
-// `one_batch` false runs a part of a larger batch: the launch configuration
-// is then the multi-object one even for a single object, so that every part
-// computes exactly what the whole batch would.
-Rows batch_rows(int64_t n_obj, const lsp_grid* grid, bool one_batch) {
+// A call may be a part of a batch of n_batch objects: the launch configuration
+// is then that batch's, so that every part computes exactly what the whole
+// would.
+Rows batch_rows(int64_t n_obj, const lsp_grid* grid, int64_t n_batch) {
     Rows r = whole_grid(n_obj, grid);
-    r.whole = one_batch;
+    r.whole = n_batch == 1;
+    r.n_batch = n_batch;
     return r;
 }
 
 size_t batch_workspace_bytes(int64_t n_obj, int64_t n_obs, const lsp_grid* grid,
-                             const lsp_options* opt_in, bool gen, bool one_batch) {
+                             const lsp_options* opt_in, bool gen, int64_t n_batch) {
     if (n_obj < 1 || n_obs < 0 || !valid_grid(grid)) return 0;
     const lsp_options opt = opt_in ? *opt_in : lsp_default_options();
     if (valid_options(&opt) != LSP_OK) return 0;
-    const Rows rows = batch_rows(n_obj, grid, one_batch);
+    const Rows rows = batch_rows(n_obj, grid, n_batch);
     Method method;
     method.gen = gen;
     Config c;
@@ -610,12 +633,12 @@ size_t batch_workspace_bytes(int64_t n_obj, int64_t n_obs, const lsp_grid* grid,
 lsp_status batch_call(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const double* t,
                       const double* y, const double* dy, bool gen, const lsp_grid* grid,
                       const lsp_options* opt, void* pgram, lsp_peak* peaks, void* ws,
-                      size_t ws_bytes, void* stream, bool one_batch) {
+                      size_t ws_bytes, void* stream, int64_t n_batch) {
     Method method;
     method.gen = gen;
     method.dy = dy;
     return run(offsets, n_obj, n_obs, t, y, grid, opt, pgram, peaks, ws, ws_bytes, stream,
-               batch_rows(n_obj, grid, one_batch), method);
+               batch_rows(n_obj, grid, n_batch), method);
 }
 
 }  // namespace lsp
@@ -682,7 +705,7 @@ static size_t rows_workspace_bytes(int64_t n_obj, int64_t n_obs, const lsp_grid*
     // Any non-null band pointer stands for "banded" when sizing.
     static const int32_t kBanded = 0;
     const lsp::Rows rows{nullptr, band_bins > 0 ? &kBanded : nullptr, n_rows, band_bins,
-                         rows_per_group, false};
+                         rows_per_group, false, n_obj};
     if (lsp::valid_rows(rows, grid) != LSP_OK) return 0;
     lsp::Config c;
     if (lsp::resolve(n_obj, n_obs, grid, &opt, rows, &c, method) != LSP_OK) return 0;
@@ -787,7 +810,7 @@ static lsp_status batch_rows(const int64_t* offsets, int64_t n_obj, int64_t n_ob
     if (!offsets) return LSP_EINVAL;
     if (!row_obj && n_rows != n_obj * (int64_t)rows_per_group) return LSP_EINVAL;
     if (!row_band) band_bins = grid ? grid->n_f : 0;
-    const lsp::Rows rows{row_obj, row_band, n_rows, band_bins, rows_per_group, false};
+    const lsp::Rows rows{row_obj, row_band, n_rows, band_bins, rows_per_group, false, n_obj};
     return lsp::run(offsets, n_obj, n_obs, t, y, grid, opt, pgram, peaks, workspace,
                     workspace_bytes, stream, rows, method);
 }

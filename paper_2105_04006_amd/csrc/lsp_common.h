@@ -41,13 +41,15 @@ struct ObjMeta {
     double t0;       // time origin: mid-point of the object's time span
     double scale;    // factor from P_LS to the reported power
     int32_t status;  // LSP_OBJ_*
-    int32_t exps;    // powers of two that scale the matrix-core factors (mx_exp_y, mx_exp_w)
+    int32_t exps;    // powers of two that scale the matrix-core factors (mx_pack_exps)
     double wnorm;    // generalized form: N / sum(1/dy^2) (1 for unit errors)
 };
 static_assert(sizeof(ObjMeta) == 64, "ObjMeta layout");
 
-// Bins of a fix-up tile of the matrix-core kernels (lsp_mx.hip).
+// Bins of a fix-up tile of the FP32 matrix-core kernels (lsp_mx.hip), and of a
+// peak record of the FP64 ones (lsp_fx.hip).
 constexpr int kMxTile = 1024;
+constexpr int kFxTile = 512;
 
 // The matrix-core kernels scale an object's centred magnitudes by 2^e with
 // max |y - ybar| 2^e in [2^13, 2^14): the products with cosines stay below
@@ -57,11 +59,20 @@ constexpr int kMxTile = 1024;
 __device__ __forceinline__ int mx_scale_exp(double largest) {
     if (!(largest > 0.0) || !isfinite(largest)) return 0;
     const int e = 13 - ilogb(largest);
-    return e < -1000 ? -1000 : (e > 1000 ? 1000 : e);
+    return e < -500 ? -500 : (e > 500 ? 500 : e);
 }
-__device__ __forceinline__ int32_t mx_pack_exps(int y, int w) { return (y & 0xffff) | (w << 16); }
-__device__ __forceinline__ int mx_exp_y(const ObjMeta& m) { return (int)(int16_t)(m.exps & 0xffff); }
-__device__ __forceinline__ int mx_exp_w(const ObjMeta& m) { return m.exps >> 16; }
+// The smallest power of two that is above the times' reach |t - t0|.
+__device__ __forceinline__ int mx_reach_exp(double reach) {
+    return reach > 0.0 && isfinite(reach) ? ilogb(reach) + 1 : -1000;
+}
+// y and w in 10 bits each, the reach in 12, all signed.
+__device__ __forceinline__ int32_t mx_pack_exps(int y, int w, int reach) {
+    return (int32_t)(((uint32_t)y & 0x3ffu) | (((uint32_t)w & 0x3ffu) << 10) |
+                     ((uint32_t)reach << 20));
+}
+__device__ __forceinline__ int mx_exp_y(const ObjMeta& m) { return (int32_t)((uint32_t)m.exps << 22) >> 22; }
+__device__ __forceinline__ int mx_exp_w(const ObjMeta& m) { return (int32_t)((uint32_t)m.exps << 12) >> 22; }
+__device__ __forceinline__ int mx_exp_reach(const ObjMeta& m) { return m.exps >> 20; }
 
 // Best (power, index) of one frequency tile; index -1 means none.
 struct PeakRec {
@@ -173,22 +184,24 @@ __device__ __forceinline__ void sums64_add(Sums64& a, double yj, double s, doubl
 // a = w tau through the sums at angle 2wt, which are (cc - ss, 2 cs); Eq. 2's
 // shifted sums then follow from the angle-difference identities.  P_LS is
 // multiplied by `scale`.
-__device__ __forceinline__ double power64(const Sums64& s, double n, double scale) {
-    const double c2 = s.cc - s.ss;
-    const double s2 = 2.0 * s.cs;
+__device__ __forceinline__ double power64_shifted(double xc, double xs, double c2, double s2,
+                                                  double tot, double n, double scale) {
     const double two_a = atan2(s2, c2);
     double sa, ca;
     sincos(0.5 * two_a, &sa, &ca);
-    const double ycs = ca * s.xc + sa * s.xs;                 // sum y cos w(t - tau)
-    const double ysn = ca * s.xs - sa * s.xc;                 // sum y sin w(t - tau)
+    const double ycs = ca * xc + sa * xs;                     // sum y cos w(t - tau)
+    const double ysn = ca * xs - sa * xc;                     // sum y sin w(t - tau)
     const double rot = c2 * (ca * ca - sa * sa) + s2 * (2.0 * sa * ca);  // sum cos 2w(t - tau)
-    const double tot = s.cc + s.ss;
     const double dcos = 0.5 * (tot + rot);                    // sum cos^2 w(t - tau)
     const double dsin = 0.5 * (tot - rot);                    // sum sin^2 w(t - tau)
     double p = 0.0;
     if (dcos > kDenEps * n) p += ycs * ycs / dcos;
     if (dsin > kDenEps * n) p += ysn * ysn / dsin;
     return 0.5 * p * scale;
+}
+
+__device__ __forceinline__ double power64(const Sums64& s, double n, double scale) {
+    return power64_shifted(s.xc, s.xs, s.cc - s.ss, 2.0 * s.cs, s.cc + s.ss, n, scale);
 }
 
 // Power from FP32 sums (cc = sum cos^2, cs = sum cos sin; sum sin^2 = N - cc).
@@ -656,12 +669,16 @@ hipError_t launch_stage(const ObjMeta* meta, const double* t, const double* y, i
                         double step_cyc, int trig, double* stage_t, float4* stage_o,
                         hipStream_t s);
 hipError_t launch_gen_fp32p(const MainParams& p, int k, int waves, hipStream_t s);
-// Matrix-core sums (lsp_mx.hip): `waves` (2 or 4; 4 for the generalized form)
+// Matrix-core sums (lsp_mx.hip): `waves` (1, 2 or 4; 4 for the generalized form)
 // tiles of 2,048 (generalized 1,024) bins per workgroup, or, with `split`, one
 // tile whose observations the waves share.
 int64_t mx_item_bins(int waves, bool split, bool gen);
 hipError_t launch_mx(const MainParams& p, int waves, bool split, hipStream_t s);
 hipError_t launch_gen_fp64(const MainParams& p, int kf, int waves, hipStream_t s);
+// FP64 sums on the matrix cores (lsp_fx.hip): four 512-bin tiles per workgroup,
+// or, with `split`, one tile whose observations 4 or 8 waves share.
+int64_t fx_item_bins(int waves, bool split);
+hipError_t launch_fx(const MainParams& p, int waves, bool split, hipStream_t s);
 hipError_t launch_fixup(const FixupParams& p, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_peaks(const PeakParams& p, hipStream_t s);
@@ -686,15 +703,14 @@ struct OrderParams {
 hipError_t launch_row_order(const OrderParams& p, hipStream_t s);
 
 // Host side (lsp_api.hip): the whole-grid batch call of lsp_batch /
-// lsp_gen_batch and its workspace size.  one_batch = false treats the objects
-// as a part of a larger batch (the multi-object launch configuration even for
-// one object).
+// lsp_gen_batch and its workspace size; the objects may be a part of a batch of
+// n_batch, whose launch configuration the call then takes.
 size_t batch_workspace_bytes(int64_t n_obj, int64_t n_obs, const lsp_grid* grid,
-                             const lsp_options* opt, bool gen, bool one_batch);
+                             const lsp_options* opt, bool gen, int64_t n_batch);
 lsp_status batch_call(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const double* t,
                       const double* y, const double* dy, bool gen, const lsp_grid* grid,
                       const lsp_options* opt, void* pgram, lsp_peak* peaks, void* ws,
-                      size_t ws_bytes, void* stream, bool one_batch);
+                      size_t ws_bytes, void* stream, int64_t n_batch);
 
 
 }  // namespace lsp

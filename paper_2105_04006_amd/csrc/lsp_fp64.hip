@@ -9,8 +9,8 @@
 // exactly before the library call, which keeps the library on its
 // short-argument path and the phase accurate to its last rounding.
 //
-// This file also holds the FP64 fix-up of the FP32 form (fixup_kernel), for
-// the standard and the generalized periodogram.
+// It runs when a launch shape is asked for; otherwise the FP64 form's sums are
+// taken on the matrix cores (lsp_fx.hip).
 //
 // Work decomposition: a workgroup of W wavefronts owns one (object, frequency
 // tile) item; the object is staged through LDS in chunks of kTile observations
@@ -114,59 +114,6 @@ __global__ __launch_bounds__(kWave* W) void fp64_kernel(const MainParams P) {
     }
 }
 
-// FP64 recompute of FP32-form tiles flagged ill-conditioned.  Workgroups stride
-// over the tiles' flag bits 256 at a time, collect the flagged ones in LDS, and
-// recompute every bin of each such tile from the FP64 series (rounding the
-// power to FP32 so the argmax still compares FP32 values), then rewrite the
-// tile's periodogram bins and merge its best bin into the group's peak key.
-constexpr int kFixThreads = 256;
-
-__global__ __launch_bounds__(kFixThreads) void fixup_kernel(const FixupParams P) {
-    __shared__ int64_t s_list[kFixThreads];
-    __shared__ int s_count;
-    __shared__ PeakRec s_red[kFixThreads / kWave];
-    for (int64_t base = (int64_t)blockIdx.x * kFixThreads; base < P.n_tiles;
-         base += (int64_t)gridDim.x * kFixThreads) {
-        if (threadIdx.x == 0) s_count = 0;
-        __syncthreads();
-        const int64_t mine = base + threadIdx.x;
-        if (mine < P.n_tiles && ((P.ill_bits[mine >> 5] >> (mine & 31)) & 1u))
-            s_list[atomicAdd(&s_count, 1)] = mine;
-        __syncthreads();
-        const int count = uniform_i32(s_count);
-        for (int q = 0; q < count; ++q) {
-            const int64_t tile = uniform_i64(s_list[q]);
-            const int64_t row = tile / P.tiles_per_row;
-            const RowRange rr =
-                decode_row(P.row_obj, P.row_band, P.band_bins, P.rows_per_group, P.n_obj, P.n_f, row);
-            const int64_t obj = rr.obj < 0 ? 0 : rr.obj;
-            const int64_t f0 = rr.f_lo + (tile - row * P.tiles_per_row) * P.tile_freqs;
-            const ObjMeta m = P.meta[obj];
-            PeakRec best{0.0, -1};
-            for (int64_t i = f0 + threadIdx.x; i < f0 + P.tile_freqs && i < rr.f_hi;
-                 i += kFixThreads) {
-                const double f = grid_freq(P.f_min, P.df, i) * P.to_cyc;
-                const double p = (double)(float)(P.gen ? power64_gen_bin(m, P.t, P.y, P.dy, f)
-                                                       : power64_bin(m, P.t, P.y, f));
-                if (P.pgram) store_pgram(P.pgram, P.pgram_f64, obj * P.n_f + i, p);
-                if (better(p, i, best.p, best.i)) best = PeakRec{p, i};
-            }
-            best = wave_best(best);
-            if ((threadIdx.x & (kWave - 1)) == 0) s_red[threadIdx.x / kWave] = best;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                PeakRec b = s_red[0];
-                for (int w = 1; w < kFixThreads / kWave; ++w)
-                    if (better(s_red[w].p, s_red[w].i, b.p, b.i)) b = s_red[w];
-                if (rr.obj >= 0 && b.i >= 0)
-                    atomicMax(&P.keys[row / P.rows_per_group], peak_key(b.p, b.i));
-            }
-            __syncthreads();
-        }
-        __syncthreads();
-    }
-}
-
 template <int KF>
 hipError_t launch_kf(const MainParams& p, int waves, hipStream_t s) {
     const dim3 grid = grid_for(p.n_items);
@@ -180,14 +127,6 @@ hipError_t launch_kf(const MainParams& p, int waves, hipStream_t s) {
 }
 
 }  // namespace
-
-hipError_t launch_fixup(const FixupParams& p, hipStream_t s) {
-    if (p.n_tiles <= 0) return hipSuccess;
-    int64_t blocks = (p.n_tiles + kFixThreads - 1) / kFixThreads;
-    if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(fixup_kernel, dim3((unsigned)blocks), dim3(kFixThreads), 0, s, p);
-    return hipGetLastError();
-}
 
 hipError_t launch_fp64(const MainParams& p, int kf, int waves, hipStream_t s) {
     if (p.n_items <= 0) return hipSuccess;

@@ -1,0 +1,435 @@
+// lsp_fx.h -- FP64 sums on the matrix cores, shared by the FP64 form and the
+// FP64 fix-up of the FP32 forms.
+//
+// As in lsp_mx.hip, a bin's frequency is a block centre plus or minus an
+// offset, f = G_a +- H_m (32 bins per block), and the angle-addition formulas
+// turn the sums over observations into products of centre factors and offset
+// factors, here in FP64 on v_mfma_f64_16x16x4_f64.  Every factor is an FP64
+// sine and cosine of an exactly reduced phase (fx_sincos), one pair per
+// (block or offset, observation) instead of one per (bin, observation).
+//
+// The grid's frequencies are rounded (grid_freq), so f_i = G_a +- H_m + e with a
+// residual e of about one unit in the last place, which the phases of a long
+// span can see (2 pi e tau ~ 1e-10).  It is applied to first order,
+//   sum v exp(2 pi i f tau) = S + 2 pi i e D,   D = sum v tau exp(2 pi i (G +- H) tau),
+// and since e is that small D needs few digits: it is accumulated from f16
+// factors on v_mfma_f32_16x16x32_f16.  Where 2 pi e tau could exceed 1e-9
+// (kFxResidual), so that D's rounding or the second order could show, the bins
+// are evaluated one by one instead (power64_bin), as are those of objects of up
+// to four points, whose moment matrix is often close to singular.
+//
+// Per four observations a 512-bin tile takes eight matrix instructions (512
+// cycles at their rate of 16 multiply-adds a cycle) and about 70 FP64 vector
+// instructions for its factors, which the FP64 units execute in turn: the two
+// bound it together.  Measured, a sine and cosine per (bin, observation) ->
+// here: 48 objects of 50..1,000 points on 40,000 bins 1984 -> 388 us; 256
+// points on 10,000 bins 82 -> 24 us; 100 objects of 520 points on 40,000 bins
+// 3.9e12 (observation, bin) pairs a second; the FP64 recompute of 300
+// asteroid-like objects 1370 -> 160 us.  The error against an extended-
+// precision evaluation is unchanged (3.8e-15 of the 2-norm).
+//
+// A bin whose smaller denominator (N - R, or T - R) is at most N/256 loses more
+// than two digits of it to cancellation; its sums are taken again term by term
+// (fx_bin_wave), the observations shared out over the wavefront.
+#pragma once
+
+#include "lsp_common.h"
+
+namespace lsp {
+
+typedef double fx_d4 __attribute__((ext_vector_type(4)));
+typedef float fx_f4 __attribute__((ext_vector_type(4)));
+typedef float fx_f2 __attribute__((ext_vector_type(2)));
+typedef _Float16 fx_h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 fx_h8 __attribute__((ext_vector_type(8)));
+
+constexpr int kFxOffs = 16;             // offsets per block
+constexpr int kFxBlk = 2 * kFxOffs;     // bins per block
+constexpr int kFxBins = 16 * kFxBlk;    // 512 bins of a wave tile
+constexpr int kFxSteps = 8;             // FP64 matrix steps (four observations) per f16 product
+constexpr int kFxObs = 256;             // observations staged per pass
+constexpr double kFxResidual = 1e-9;
+constexpr double kFxIll = 1.0 / 256.0;
+constexpr int kFxFew = 4;               // objects of up to this many points: bin by bin
+
+// Sums of a wave tile.  Complex sums: the standard form has sum y e and
+// sum e^2 / 2, the generalized one sum w e, sum w yw e and sum w e^2 / 2
+// (e = exp(2 pi i f tau)).  x[4 g + ..]: the four products of sum g,
+// d: the same with tau, in scaled units.
+template <bool GEN>
+struct FxSums {
+    static constexpr int kSums = GEN ? 3 : 2;
+    fx_d4 x[4 * kSums];
+    fx_f4 d[4 * kSums];
+};
+
+// Staged observations (LDS).  u: y - ybar (standard) or w (yw and w: w yw, w);
+// the float values are those times tau, scaled into f16's range.
+template <bool GEN>
+struct FxStage {
+    double hi[kFxObs], lo[kFxObs];
+    double u[kFxObs];                 // y - ybar, or w (y - ybar)
+    double w[GEN ? kFxObs : 1];       // generalized: weights
+    float ut[kFxObs];                 // u tau
+    float wt[kFxObs];                 // tau, or w tau
+};
+
+struct FxScales {
+    double up_u, up_w, up_t;  // powers of two: u, w and tau into f16's range
+};
+
+template <bool GEN>
+__device__ __forceinline__ FxScales fx_scales(const ObjMeta& m) {
+    FxScales s;
+    s.up_u = ldexp(1.0, mx_exp_y(m));
+    s.up_w = GEN ? ldexp(1.0, mx_exp_w(m)) : 1.0;
+    s.up_t = ldexp(1.0, -mx_exp_reach(m));  // |tau| up_t <= 1
+    return s;
+}
+
+template <bool GEN>
+__device__ __forceinline__ void fx_stage(FxStage<GEN>& S, const ObjMeta& m,
+                                         const double* __restrict__ t,
+                                         const double* __restrict__ y,
+                                         const double* __restrict__ dy, int64_t jt, int cnt,
+                                         const FxScales& sc, int threads) {
+    const int padded = (cnt + 3) / 4 * 4;
+    for (int q = threadIdx.x; q < padded; q += threads) {
+        const int64_t j = m.j0 + jt + q;
+        double hi = 0.0, lo = 0.0, u = 0.0, w = 0.0;
+        if (q < cnt) {
+            recentre64(t[j], m.t0, &hi, &lo);
+            w = GEN ? gen_weight(dy, j, m.wnorm) : 1.0;
+            u = w * (y[j] - m.ybar);
+        }
+        S.hi[q] = hi;
+        S.lo[q] = lo;
+        S.u[q] = u;
+        if (GEN) S.w[q] = w;
+        const double ts = hi * sc.up_t;
+        S.ut[q] = (float)(u * sc.up_u * ts);
+        S.wt[q] = (float)(w * sc.up_w * ts);
+    }
+}
+
+// The operand of the lane that holds row 4 b + a, for a lane of row 4 a + b.
+__device__ __forceinline__ fx_h8 fx_transpose_rows(fx_h8 v, int lane) {
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    const int from = (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3);
+    i4 x = __builtin_bit_cast(i4, v);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = __builtin_amdgcn_ds_bpermute(from << 2, x[k]);
+    return __builtin_bit_cast(fx_h8, x);
+}
+
+// sin and cos of 2 pi f (hi + lo), the phase reduced exactly as in
+// sincos_cycles64, then to a quarter turn about zero, |x| <= pi/4, and the
+// Taylor series there: to x^17 and x^16, whose first dropped terms are below
+// 2^-60.  The library function spends as many FP64 operations and, on its
+// selections for arguments that cannot occur here, about forty more.
+__device__ __forceinline__ void fx_sincos(double f, double hi, double lo, double* sn, double* cs) {
+    double r;
+    {
+#pragma clang fp contract(off)
+        const double p = f * hi;
+        const double e = fma(f, hi, -p);
+        r = (p - rint(p)) + fma(f, lo, e);
+    }
+    const double k = rint(4.0 * r);
+    const double x = kTwoPi * fma(-0.25, k, r);
+    const double z = x * x;
+    double ps = fma(z, 1.0 / 355687428096000.0, -1.0 / 1307674368000.0);
+    ps = fma(z, ps, 1.0 / 6227020800.0);
+    ps = fma(z, ps, -1.0 / 39916800.0);
+    ps = fma(z, ps, 1.0 / 362880.0);
+    ps = fma(z, ps, -1.0 / 5040.0);
+    ps = fma(z, ps, 1.0 / 120.0);
+    ps = fma(z, ps, -1.0 / 6.0);
+    const double s0 = fma(x * z, ps, x);
+    double pc = fma(z, 1.0 / 20922789888000.0, -1.0 / 87178291200.0);
+    pc = fma(z, pc, 1.0 / 479001600.0);
+    pc = fma(z, pc, -1.0 / 3628800.0);
+    pc = fma(z, pc, 1.0 / 40320.0);
+    pc = fma(z, pc, -1.0 / 720.0);
+    pc = fma(z, pc, 1.0 / 24.0);
+    pc = fma(z, pc, -0.5);
+    const double c0 = fma(z, pc, 1.0);
+    // rotate by k quarter turns: swap on odd k, then the signs
+    const int q = (int)(float)k;
+    const double sx = (q & 1) ? c0 : s0, cx = (q & 1) ? s0 : c0;
+    const uint64_t top = 1ull << 63;
+    *sn = __longlong_as_double(__double_as_longlong(sx) ^ ((q & 2) ? top : 0ull));
+    *cs = __longlong_as_double(__double_as_longlong(cx) ^ (((q + 1) & 2) ? top : 0ull));
+}
+
+// Add the steps [lo, hi) of four staged observations each to the wave's sums.
+// Lane (row or column lane % 16, quarter lane / 16) supplies observation
+// 4 step + quarter to both operands; eight steps feed one f16 product.
+template <bool GEN>
+__device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>& S, int cnt,
+                                              int lo, int hi, double G, double H, int lane) {
+    constexpr int NG = FxSums<GEN>::kSums;
+    const int quarter = lane >> 4;
+    for (int s0 = lo; s0 < hi; s0 += kFxSteps) {
+        const int steps = hi - s0 < kFxSteps ? hi - s0 : kFxSteps;
+        fx_h8 ah[2 * NG], bh[4];
+#pragma unroll
+        for (int q = 0; q < 2 * NG; ++q) ah[q] = fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bh[q] = fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < kFxSteps; ++s) {
+            if (s < steps) {
+                const int j = 4 * (s0 + s) + quarter;
+                const double th = S.hi[j], tl = S.lo[j], u = S.u[j];
+                const double one = j < cnt ? 1.0 : 0.0;  // padding weighs nothing
+                double sn, cs;
+                fx_sincos(G, th, tl, &sn, &cs);
+                const double w = GEN ? S.w[j] : one;
+                const double c2 = w * fma(cs, cs, -0.5), s2 = w * (cs * sn);
+                double a[2 * NG];
+                a[0] = (GEN ? w : u) * cs;
+                a[1] = (GEN ? w : u) * sn;
+                if (GEN) {
+                    a[2] = u * cs;
+                    a[3] = u * sn;
+                }
+                a[2 * NG - 2] = c2;
+                a[2 * NG - 1] = s2;
+                const float cf = (float)cs, sf = (float)sn, ut = S.ut[j], wt = S.wt[j];
+                ah[0][s] = (_Float16)((GEN ? wt : ut) * cf);
+                ah[1][s] = (_Float16)((GEN ? wt : ut) * sf);
+                if (GEN) {
+                    ah[2][s] = (_Float16)(ut * cf);
+                    ah[3][s] = (_Float16)(ut * sf);
+                }
+                ah[2 * NG - 2][s] = (_Float16)(wt * fmaf(cf, cf, -0.5f));
+                ah[2 * NG - 1][s] = (_Float16)(wt * (cf * sf));
+                double bs, bc;
+                fx_sincos(H, th, tl, &bs, &bc);
+                const double b2c = fma(bc, bc, -0.5), b2s = bc * bs;
+                const float bcf = (float)bc, bsf = (float)bs;
+                const fx_h2 b1 = __builtin_convertvector((fx_f2){bcf, bsf}, fx_h2);
+                bh[0][s] = b1.x;
+                bh[1][s] = b1.y;
+                bh[2][s] = (_Float16)fmaf(bcf, bcf, -0.5f);
+                bh[3][s] = (_Float16)(bcf * bsf);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const double c = g + 1 == NG ? b2c : bc, z = g + 1 == NG ? b2s : bs;
+                    A.x[4 * g + 0] =
+                        __builtin_amdgcn_mfma_f64_16x16x4f64(a[2 * g], c, A.x[4 * g + 0], 0, 0, 0);
+                    A.x[4 * g + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2 * g + 1], z,
+                                                                         A.x[4 * g + 1], 0, 0, 0);
+                    A.x[4 * g + 2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2 * g + 1], c,
+                                                                         A.x[4 * g + 2], 0, 0, 0);
+                    A.x[4 * g + 3] =
+                        __builtin_amdgcn_mfma_f64_16x16x4f64(a[2 * g], z, A.x[4 * g + 3], 0, 0, 0);
+                }
+            }
+        }
+        // the FP64 product leaves block row 4 r + quarter in element r, the f16
+        // one row 4 quarter + r: transpose the rows that feed the latter
+#pragma unroll
+        for (int q = 0; q < 2 * NG; ++q) ah[q] = fx_transpose_rows(ah[q], lane);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const fx_h8 c = bh[g + 1 == NG ? 2 : 0], z = bh[g + 1 == NG ? 3 : 1];
+            A.d[4 * g + 0] =
+                __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2 * g], c, A.d[4 * g + 0], 0, 0, 0);
+            A.d[4 * g + 1] =
+                __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2 * g + 1], z, A.d[4 * g + 1], 0, 0, 0);
+            A.d[4 * g + 2] =
+                __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2 * g + 1], c, A.d[4 * g + 2], 0, 0, 0);
+            A.d[4 * g + 3] =
+                __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2 * g], z, A.d[4 * g + 3], 0, 0, 0);
+        }
+    }
+}
+
+template <bool GEN>
+__device__ __forceinline__ void fx_zero(FxSums<GEN>& A) {
+#pragma unroll
+    for (int q = 0; q < 4 * FxSums<GEN>::kSums; ++q) {
+        A.x[q] = fx_d4{0.0, 0.0, 0.0, 0.0};
+        A.d[q] = fx_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+
+__device__ __forceinline__ double fx_wave_sum(double v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+// Power at frequency f (cycles; the same in every lane) from sums taken term by
+// term, the observations shared out over the wavefront.  Called by all lanes.
+template <bool GEN>
+__device__ __noinline__ double fx_bin_wave(const ObjMeta& m, const double* __restrict__ t,
+                                           const double* __restrict__ y,
+                                           const double* __restrict__ dy, double f, int lane) {
+    double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int64_t j = m.j0 + lane; j < m.j0 + m.n; j += kWave) {
+        double s, c, hi, lo;
+        recentre64(t[j], m.t0, &hi, &lo);
+        sincos_cycles64(f, hi, lo, &s, &c);
+        const double w = GEN ? gen_weight(dy, j, m.wnorm) : 1.0;
+        const double u = w * (y[j] - m.ybar);
+        if (GEN) {
+            v[5] += w * c;
+            v[6] += w * s;
+        }
+        v[0] = fma(u, c, v[0]);
+        v[1] = fma(u, s, v[1]);
+        v[2] = fma(w * c, c, v[2]);
+        v[3] = fma(w * s, s, v[3]);
+        v[4] = fma(w * c, s, v[4]);
+    }
+#pragma unroll
+    for (int q = 0; q < (GEN ? 7 : 5); ++q) v[q] = fx_wave_sum(v[q]);
+    if (GEN)
+        return power64_gen(SumsGen64{v[5], v[6], v[0], v[1], v[2], v[3], v[4]}, (double)m.n,
+                           m.scale);
+    return power64(Sums64{v[0], v[1], v[2], v[3], v[4]}, (double)m.n, m.scale);
+}
+
+// Power of the bin at frequency f (cycles) = G + side H + e from the products
+// x and d of its block and offset (side -1 or +1); `in`: the bin exists.
+// Called by all lanes of the wavefront.
+template <bool GEN>
+__device__ __forceinline__ double fx_power(const double (&x)[4 * FxSums<GEN>::kSums],
+                                           const float (&d)[4 * FxSums<GEN>::kSums], double f,
+                                           double G, double H, double side, const ObjMeta& m,
+                                           const FxScales& sc, const double* __restrict__ t,
+                                           const double* __restrict__ y,
+                                           const double* __restrict__ dy, bool in, int lane) {
+    constexpr int NG = FxSums<GEN>::kSums;
+    const double h = side * H;
+    double e;  // f - (G + h), the sum's rounding error included (two-sum)
+    {
+#pragma clang fp contract(off)
+        const double s = G + h;
+        const double bb = s - G;
+        const double err = (G - (s - bb)) + (h - bb);
+        e = (f - s) - err;
+    }
+    double re[NG], im[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const bool weighted = GEN ? g == 1 : g == 0;  // sums of u, else of w
+        const double back = (kTwoPi * e) * (1.0 / ((weighted ? sc.up_u : sc.up_w) * sc.up_t)) *
+                            (g + 1 == NG ? 2.0 : 1.0);
+        const double dr = (double)d[4 * g] - side * (double)d[4 * g + 1];
+        const double di = (double)d[4 * g + 2] + side * (double)d[4 * g + 3];
+        re[g] = fma(-back, di, x[4 * g] - side * x[4 * g + 1]);
+        im[g] = fma(back, dr, x[4 * g + 2] + side * x[4 * g + 3]);
+    }
+    // the double-angle factors are halves on both sides
+    const double c2 = 4.0 * re[NG - 1], s2 = 4.0 * im[NG - 1];
+    const double n = (double)m.n;
+    double p, tr = n, dd = c2, ee = s2;  // trace, and the difference R = |(dd, ee)|
+    if (GEN) {
+        const double rn = 1.0 / n;
+        tr = n - (re[0] * re[0] + im[0] * im[0]) * rn;
+        dd = c2 - (re[0] * re[0] - im[0] * im[0]) * rn;
+        ee = s2 - 2.0 * re[0] * im[0] * rn;
+        p = power64_gen(SumsGen64{re[0], im[0], re[1], im[1], 0.5 * (n + c2), 0.5 * (n - c2),
+                                  0.5 * s2},
+                        n, m.scale);
+    } else {
+        p = power64_shifted(re[0], im[0], c2, s2, n, n, m.scale);
+    }
+    const double edge = tr - kFxIll * n;
+    unsigned long long ill = __ballot(in && !(edge > 0.0 && dd * dd + ee * ee < edge * edge));
+    while (ill) {
+        const int l = __builtin_ctzll(ill);
+        ill &= ill - 1;
+        const double q = fx_bin_wave<GEN>(m, t, y, dy, __shfl(f, l, kWave), lane);
+        if (lane == l) p = q;
+    }
+    return p;
+}
+
+// Whether the object's bins, whose frequencies (cycles) are at most f_top in
+// size, go through the matrix cores: the first-order residual covers them, and
+// there are more than a few points.
+__device__ __forceinline__ bool fx_covers(double f_top, const ObjMeta& m) {
+    return m.n > kFxFew && kTwoPi * 2.220446049250313e-16 * f_top * ldexp(1.0, mx_exp_reach(m)) <= kFxResidual;
+}
+
+// Wave w's share [lo, hi) of the steps of cnt staged observations.
+template <int W>
+__device__ __forceinline__ void fx_share(int cnt, int wave, int* lo, int* hi) {
+    const int steps = (cnt + 3) / 4, per = (steps + W - 1) / W;
+    *lo = wave * per < steps ? wave * per : steps;
+    *hi = *lo + per < steps ? *lo + per : steps;
+}
+
+// The sums over the W waves of a workgroup, in wave order, of accumulator row
+// `wave` (of the lane's four; waves from 4 on take part in the exchange only).
+// Each round passes two of the products through LDS (d: four, as floats).
+template <bool GEN, int W>
+__device__ __forceinline__ void fx_gather(const FxSums<GEN>& A, double (*buf)[8][kWave], int wave,
+                                          int lane, double (&x)[4 * FxSums<GEN>::kSums],
+                                          float (&d)[4 * FxSums<GEN>::kSums]) {
+    constexpr int NQ = 4 * FxSums<GEN>::kSums;
+#pragma unroll
+    for (int q = 0; q < NQ; q += 2) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) buf[wave][r][lane] = A.x[q + r / 4][r % 4];
+        __syncthreads();
+        if (wave < 4) {
+            double v0 = 0.0, v1 = 0.0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                v0 += buf[w][wave][lane];
+                v1 += buf[w][4 + wave][lane];
+            }
+            x[q] = v0;
+            x[q + 1] = v1;
+        }
+    }
+    float (*fbuf)[16][kWave] = reinterpret_cast<float (*)[16][kWave]>(buf);
+#pragma unroll
+    for (int q = 0; q < NQ; q += 4) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) fbuf[wave][r][lane] = A.d[q + r / 4][r % 4];
+        __syncthreads();
+        if (wave < 4)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = 0.0f;
+#pragma unroll
+                for (int w = 0; w < W; ++w) v += fbuf[w][4 * e + wave][lane];
+                d[q + e] = v;
+            }
+    }
+}
+
+// Power of one bin on its own, term by term (fx_covers); not inlined, so that
+// its registers stay out of the callers' loops.
+template <bool GEN>
+__device__ __noinline__ double fx_bin(const ObjMeta& m, const double* __restrict__ t,
+                                      const double* __restrict__ y, const double* __restrict__ dy,
+                                      double f) {
+    return GEN ? power64_gen_bin(m, t, y, dy, f) : power64_bin(m, t, y, f);
+}
+
+// Centre frequency of a block row, and offset of a column, in cycles, for the
+// tile whose first bin is w0.  Never contracted: the sums and the residual
+// (fx_power) must see the same value.
+__device__ __forceinline__ double fx_centre(double f_min, double df, double to_cyc, int64_t w0,
+                                            int row) {
+#pragma clang fp contract(off)
+    return (f_min + df * ((double)(w0 + (int64_t)row * kFxBlk) + (kFxOffs - 0.5))) * to_cyc;
+}
+__device__ __forceinline__ double fx_offset(double df, double to_cyc, int col) {
+#pragma clang fp contract(off)
+    return (df * to_cyc) * ((double)col + 0.5);
+}
+// Accumulator element r of lane l holds block row 4 r + l / 16, offset l % 16.
+__device__ __forceinline__ int fx_row(int r, int lane) { return 4 * r + (lane >> 4); }
+
+}  // namespace lsp

@@ -215,7 +215,7 @@ lsp_status run_lane(lsp_pipe p, int lane, const int64_t* offsets, int64_t n_obj,
         lsp_status st = lsp::batch_call(offsets + o0, m, n_obs, t, y, dy, gen, grid, opt,
                                         host_pgram ? L.d_pgram[b] : nullptr,
                                         static_cast<lsp_peak*>(L.d_peaks[b]), L.d_ws,
-                                        L.d_ws_bytes, L.stream, n_obj == 1);
+                                        L.d_ws_bytes, L.stream, n_obj);
         if (st != LSP_OK) return st;
         return hipEventRecord(L.computed[b], L.stream) == hipSuccess ? LSP_OK : LSP_EHIP;
     };
@@ -338,7 +338,7 @@ static lsp_status batch_to_host(lsp_pipe pipe, const int64_t* offsets, int64_t n
     const lsp_options opt = opt_in ? *opt_in : lsp_default_options();
     if (opt.t_split > 1) return LSP_EUNSUPPORTED;
     const bool gen = generalized != 0;
-    if (lsp::batch_workspace_bytes(1, n_obs, grid, &opt, gen, n_obj == 1) == 0) return LSP_EINVAL;
+    if (lsp::batch_workspace_bytes(1, n_obs, grid, &opt, gen, n_obj) == 0) return LSP_EINVAL;
     const size_t bin_bytes = opt.pgram_dtype == LSP_PGRAM_F64 ? 8 : 4;
     const size_t row_bytes = bin_bytes * (size_t)grid->n_f;
     // Objects per chunk: about chunk_bytes of periodogram (at least one
@@ -351,7 +351,7 @@ static lsp_status batch_to_host(lsp_pipe pipe, const int64_t* offsets, int64_t n
     // Every chunk runs with the launch configuration of the whole batch (so
     // its results are lsp_batch's bit for bit); a chunk of the largest size
     // needs the most workspace.
-    const size_t ws = lsp::batch_workspace_bytes(chunk, n_obs, grid, &opt, gen, n_obj == 1);
+    const size_t ws = lsp::batch_workspace_bytes(chunk, n_obs, grid, &opt, gen, n_obj);
     if (ws == 0) return LSP_EUNSUPPORTED;
     // Device buffers for one chunk per stream (kept for later calls).
     for (int i = 0; i < pipe->n_streams; ++i) {

@@ -336,8 +336,8 @@ __global__ __launch_bounds__(kWave* W, 2) void mx_tile_kernel(const MainParams P
 }
 
 // One 32 x 32 tile per workgroup of eight waves, which share out the
-// observations in slices and add their sums through LDS in wave order: for a
-// single series, whose tiles alone are too few to fill the chip.
+// observations in slices and add their sums through LDS in wave order: for
+// calls whose tiles alone are too few to fill the chip.
 constexpr int kSplitW = 8;
 constexpr int kSplitObs = 1024;  // observations staged per pass
 
@@ -822,6 +822,8 @@ hipError_t launch_mx(const MainParams& p, int waves, bool split, hipStream_t s) 
         hipLaunchKernelGGL(mx_tile_kernel<4>, grid, dim3(kWave * 4), 0, s, p);
     } else if (waves == 2) {
         hipLaunchKernelGGL(mx_tile_kernel<2>, grid, dim3(kWave * 2), 0, s, p);
+    } else if (waves == 1) {
+        hipLaunchKernelGGL(mx_tile_kernel<1>, grid, dim3(kWave), 0, s, p);
     } else {
         return hipErrorInvalidValue;
     }

@@ -150,7 +150,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
         m.syy = syy;
         m.t0 = t0;
         m.wnorm = wnorm;
-        m.exps = mx_pack_exps(mx_scale_exp(big), P.gen ? mx_scale_exp(big_w) : 0);
+        m.exps = mx_pack_exps(mx_scale_exp(big), P.gen ? mx_scale_exp(big_w) : 0,
+                              mx_reach_exp(fmax(r.tmax - t0, t0 - r.tmin)));
         int32_t st = LSP_OBJ_OK;
         if (r.bad || (P.gen && n > 0 && !ok_w))
             st = LSP_OBJ_NONFINITE;
