@@ -4,14 +4,30 @@
 // kernels around it (softmax cross-entropy, column sums, Adam, feature
 // standardisation, top-k bands, FP32 -> BF16).
 //
-// GEMM tiling: a 256-thread workgroup (4 wavefronts) owns a 64 x 64 tile of C
-// and walks K in steps of 32.  Each step stages a 64 x 32 slice of A and a
-// 32 x 64 slice of B into LDS with K contiguous (whatever the source strides),
-// then each wavefront issues 2 x 2 v_mfma_f32_16x16x32_bf16 for its 32 x 32
-// quarter.  A lane supplies row (lane % 16) of A and column (lane % 16) of B
-// with eight consecutive k; both operands use the same k assignment, so the
-// product does not depend on how the instruction orders k internally.  The
-// 16 x 16 result is held as rows 4 (lane / 16) + r, column lane % 16.
+// GEMM.  A workgroup of four wavefronts owns a BM x BN tile of C and walks K in
+// steps of BK.  The operands of the next D steps are in flight to registers
+// while the current one's are multiplied out of LDS, and go to the other of two
+// LDS buffers, one barrier a step.  An operand whose k is contiguous is kept in
+// LDS with k contiguous, one whose rows (m of A, n of B) are contiguous with
+// its rows contiguous, so both are written as they come, 16 bytes at a time;
+// the latter is turned when it is read, by ds_read_b64_tr_b16 (four k of one
+// row per lane from four rows of 16).  Each wavefront then issues
+// v_mfma_f32_16x16x32_bf16 on its part of the tile, k in increasing blocks of
+// 32 whatever the tile, so that a result does not depend on the tile taken.
+// The instruction gets B's fragment first: its result then holds four
+// neighbouring columns of one row per lane, which are stored together.
+//
+// Rows of a ragged last tile are read as the matrix's last row, so that such a
+// tile runs at the speed of the others: four of them, taken element by element
+// without prefetch, held a whole 20,000-row product up from 54 to 69 us.
+//
+// What bounds it: at 20,000 x 1,088 x 512 the matrix cores are busy 29 % of the
+// time and LDS 43 %; the two waves a SIMD has room for (128 x 128 tiles) wait
+// for each other's LDS reads and MFMAs and for the barrier.  In a training step
+// (512 rows) every product is a latency chain of K / 64 steps.  Measured (one k
+// step of 32 per barrier pair, no prefetch -> here): 20,000 x 1,088 x 512 156 ->
+// 44 us (500 TFLOP/s), 20,000 x 512 x 256 54 -> 18 us; a training step of 512
+// rows, which was 17 launches, 199 -> 43 us in 8.
 #include <math.h>
 #include <stdint.h>
 #include <string.h>
@@ -24,9 +40,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBK = 32;
-constexpr int kLdsK = kBK + 8;  // padded row: 80 bytes, keeps 16-byte fragment reads aligned
-constexpr int kGemmThreads = 256;  // the 64 x 64 tile's four waves
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __host__ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
     uint32_t u;
@@ -54,70 +69,229 @@ struct GemmArgs {
     uint16_t* Cb;          // BF16 output or NULL
     int64_t ldc;
     int32_t a_mode, b_mode;  // how each operand is staged: kLoad*
+    int32_t c_vec;           // four neighbouring results (and mask values) move together
+    int32_t pad2;
 };
 
 // How an operand tile is read from global memory: 8 consecutive k in one
-// 16-byte load, 8 consecutive rows (m of A, n of B) in one 16-byte load that
-// is transposed on its way into LDS, or element by element.
+// 16-byte load, 8 consecutive rows (m of A, n of B) in one 16-byte load, or
+// element by element.
 enum { kLoadK = 0, kLoadRows = 1, kLoadScalar = 2 };
 
-// Stage rows [o0, o0 + BO) x k [k0, k0 + kBK) of an operand whose element
-// (o, k) is X[o * so + k * sk] into Xs[o][k] (k contiguous, padded rows);
-// outside the matrix the tile holds zeros.
-template <int BO, int NT>
-__device__ __forceinline__ void stage_operand(uint16_t* Xs, const uint16_t* X, int64_t so,
-                                              int64_t sk, int64_t O, int64_t K, int64_t o0,
-                                              int64_t k0, int mode, int tid) {
-    constexpr int kChunks = BO * (kBK / 8);  // 8 elements each
+// Strides (elements) of the 16-byte modes: a tile's places are 32-bit offsets.
+constexpr int64_t kMaxStride = 1 << 23;
+
+// One operand's tile of BO rows x BK k: 16-byte chunks per thread in registers
+// on the way from global memory to LDS.  MODE: kLoad* (kLoadScalar keeps k
+// contiguous in LDS, as kLoadK).
+template <int BO, int BK, int MODE, int D = 1>
+struct Operand {
+    static constexpr int kThreads = 256;
+    static constexpr bool kRows = MODE == kLoadRows;
+    static constexpr int kChunks = BO * BK / 8;  // 8 elements each
+    static constexpr int kPer = kChunks / kThreads;
+    static_assert(kChunks % kThreads == 0, "whole chunks per thread");
+    // padded pitch (elements) that keeps 16-byte alignment and spreads the
+    // fragment reads over the banks
+    static constexpr int kPitch = kRows ? BO + 16 : BK + 8;
+    static constexpr int kLds = (kRows ? BK : BO) * kPitch;
+    // consecutive threads take consecutive chunks of a line (a row's k, or one
+    // k's rows), and each thread the same place of kPer lines kStep apart
+    static constexpr int kLine = (kRows ? BO : BK) / 8;
+    static constexpr int kStep = kThreads / kLine;
+
+    u32x4 v[D][kPer];
+    uint32_t off[kPer];
+    int line, at;  // this thread's first line, and its element within a line
+
+    __device__ __forceinline__ Operand()
+        : line((int)threadIdx.x / kLine), at(((int)threadIdx.x % kLine) * 8) {}
+
+    // Whether fetch() serves a tile of rows from o0: it lies inside the matrix,
+    // or its rows past the end can be read as other rows of the matrix (their
+    // results are not stored).
+    static __device__ __forceinline__ bool plain(int64_t O, int64_t o0) {
+        return MODE != kLoadScalar && (o0 + BO <= O || !kRows || O % 8 == 0);
+    }
+
+    // This thread's places in a tile of rows from o0, in bytes from the tile's
+    // corner (strides are below kMaxStride).
+    __device__ __forceinline__ void place(int64_t so, int64_t sk, int64_t O, int64_t o0) {
+        const int64_t top = (kRows ? O - 8 : O - 1) - o0;
 #pragma unroll
-    for (int c0 = 0; c0 < kChunks; c0 += NT) {
-        const int c = c0 + tid;
-        if (mode == kLoadRows) {
-            // 8 consecutive rows at one k
-            const int kk = c / (BO / 8), oc = (c % (BO / 8)) * 8;
-            const int64_t o = o0 + oc, k = k0 + kk;
-            uint16_t v[8];
-            if (o + 8 <= O && k < K) {
-                const uint4 q = *reinterpret_cast<const uint4*>(X + o + k * sk);
-                memcpy(v, &q, sizeof q);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[e] = (o + e < O && k < K) ? X[(o + e) + k * sk] : 0;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) Xs[(oc + e) * kLdsK + kk] = v[e];
-        } else {
-            // 8 consecutive k of one row
-            const int oo = c / (kBK / 8), kc = (c % (kBK / 8)) * 8;
-            const int64_t o = o0 + oo, k = k0 + kc;
-            uint4 q;
-            if (mode == kLoadK && o < O && k + 8 <= K) {
-                q = *reinterpret_cast<const uint4*>(X + o * so + k);
-            } else {
-                uint16_t v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[e] = (o < O && k + e < K) ? X[o * so + (k + e) * sk] : 0;
-                memcpy(&q, v, sizeof q);
-            }
-            *reinterpret_cast<uint4*>(&Xs[oo * kLdsK + kc]) = q;
+        for (int i = 0; i < kPer; ++i) {
+            int64_t o = kRows ? at : line + i * kStep;
+            const int64_t k = kRows ? line + i * kStep : at;
+            o = o < top ? o : top;
+            off[i] = 2u * (uint32_t)(o * so + k * sk);
         }
     }
+
+    // The BK k from the tile's corner (o0, k0) on, into register set d.
+    __device__ __forceinline__ void fetch(int d, const uint16_t* corner) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            v[d][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(corner) +
+                                                      off[i]);
+    }
+
+    // The same at the end of k, at a ragged edge of rows and in any mode: zeros
+    // outside the matrix.
+    __device__ __forceinline__ void fetch_edge(const uint16_t* X, int64_t so, int64_t sk, int64_t O,
+                                               int64_t K, int64_t o0, int64_t k0) {
+        const int64_t o = o0 + (kRows ? at : line), k = k0 + (kRows ? line : at);
+        uint32_t part = 0u;  // chunks partly outside (or scattered)
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t oi = kRows ? o : o + i * kStep, ki = kRows ? k + i * kStep : k;
+            v[0][i] = u32x4{0u, 0u, 0u, 0u};
+            if (oi < O && ki < K) {
+                if (MODE != kLoadScalar && (kRows ? oi + 8 <= O : ki + 8 <= K))
+                    v[0][i] = *reinterpret_cast<const u32x4*>(X + oi * so + ki * sk);
+                else
+                    part |= 1u << i;
+            }
+        }
+        if (!part) return;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (!((part >> i) & 1u)) continue;
+            const int64_t oi = kRows ? o : o + i * kStep, ki = kRows ? k + i * kStep : k;
+            uint16_t e[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int64_t oe = kRows ? oi + r : oi, ke = kRows ? ki : ki + r;
+                e[r] = oe < O && ke < K ? X[oe * so + ke * sk] : 0;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[0][i][r] = e[2 * r] | ((uint32_t)e[2 * r + 1] << 16);
+        }
+    }
+
+    __device__ __forceinline__ void put(int d, uint16_t* L) const {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            *reinterpret_cast<u32x4*>(L + (line + i * kStep) * kPitch + at) = v[d][i];
+    }
+
+    // The fragment of rows [o, o + 16) and k [kk, kk + 32): row lane % 16,
+    // k 8 (lane / 16) + 0..7.
+    static __device__ __forceinline__ bf16x8 fragment(const uint16_t* L, int o, int kk, int lane) {
+        const int g = lane >> 4, i = lane & 15;
+        if (!kRows) return *reinterpret_cast<const bf16x8*>(L + (o + i) * kPitch + kk + 8 * g);
+        typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+        const uint16_t* src = L + (kk + 8 * g + (i >> 2)) * kPitch + o + 4 * (i & 3);
+        union {
+            s16x4 half[2];
+            bf16x8 all;
+        } f;
+        f.half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(src));
+        f.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(src + 4 * kPitch));
+        return f.all;
+    }
+};
+
+// LDS elements of a BM x BN tile's two buffers of both operands, in any mode.
+template <int BM, int BN, int BK>
+constexpr int gemm_lds() {
+    constexpr int am = Operand<BM, BK, kLoadK>::kLds > Operand<BM, BK, kLoadRows>::kLds
+                           ? Operand<BM, BK, kLoadK>::kLds
+                           : Operand<BM, BK, kLoadRows>::kLds;
+    constexpr int bm = Operand<BN, BK, kLoadK>::kLds > Operand<BN, BK, kLoadRows>::kLds
+                           ? Operand<BN, BK, kLoadK>::kLds
+                           : Operand<BN, BK, kLoadRows>::kLds;
+    return 2 * (am + bm);
 }
 
-// C (BM x BN tile per workgroup) = A B on the matrix cores: WM x WN waves,
-// each accumulating (BM / WM) x (BN / WN) from 16 x 16 x 32 BF16 products
-// into FP32.
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const GemmArgs g) {
-    constexpr int NT = 64 * WM * WN;
+// Bias, ReLU and mask on a wave's results, and their stores: fragment (i, j)
+// of the wave holds columns n + 16 j + 0..3 of row m + 16 i in this lane.
+// WHOLE: the tile lies inside C and four neighbouring results move together.
+template <int TI, int TJ, bool WHOLE>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, int64_t m, int64_t n,
+                                              f32x4 (&acc)[TI][TJ]) {
+    auto in = [&](int i, int j, int r) {
+        return WHOLE || (m + 16 * i < g.M && n + 16 * j + r < g.N);
+    };
+    if (g.bias) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            f32x4 bias;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                bias[r] = WHOLE || n + 16 * j + r < g.N ? g.bias[n + 16 * j + r] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] += bias[r];
+        }
+    }
+    if (g.relu) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = acc[i][j][r] > 0.f ? acc[i][j][r] : 0.f;
+    }
+    if (g.mask) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const uint16_t* const mk = g.mask + (m + 16 * i) * g.ldc + n;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                uint16_t e[4];
+                if (WHOLE) {
+                    const ushort4 q = *reinterpret_cast<const ushort4*>(mk + 16 * j);
+                    e[0] = q.x, e[1] = q.y, e[2] = q.z, e[3] = q.w;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) e[r] = in(i, j, r) ? mk[16 * j + r] : 0;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (!(bf16_bits_to_f32(e[r]) > 0.f)) acc[i][j][r] = 0.f;
+            }
+        }
+    }
+    auto each = [&](auto&& store) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) store(i, j, (m + 16 * i) * g.ldc + n + 16 * j);
+    };
+    if (g.Cf)
+        each([&](int i, int j, int64_t at) {
+            if (WHOLE)
+                *reinterpret_cast<f32x4*>(g.Cf + at) = acc[i][j];
+            else
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (in(i, j, r)) g.Cf[at + r] = acc[i][j][r];
+        });
+    if (g.Cb)
+        each([&](int i, int j, int64_t at) {
+            uint16_t e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[r] = f32_to_bf16_bits(acc[i][j][r]);
+            if (WHOLE)
+                *reinterpret_cast<ushort4*>(g.Cb + at) = make_ushort4(e[0], e[1], e[2], e[3]);
+            else
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (in(i, j, r)) g.Cb[at + r] = e[r];
+        });
+}
+
+// One BM x BN tile of C, by the 256 threads of a workgroup as WM x WN waves.
+template <int BM, int BN, int BK, int WM, int WN, int D, int AMODE, int BMODE>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int64_t m0, int64_t n0,
+                                          uint16_t* lds) {
+    typedef Operand<BM, BK, AMODE> OpA;
+    typedef Operand<BN, BK, BMODE> OpB;
     constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;  // 16 x 16 fragments per wave
-    __shared__ __attribute__((aligned(16))) uint16_t As[BM * kLdsK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * kLdsK];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
+    uint16_t* const As = lds;
+    uint16_t* const Bs = lds + 2 * OpA::kLds;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
 
     f32x4 acc[TI][TJ];
@@ -126,42 +300,176 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const GemmArgs 
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
-    for (int64_t k0 = 0; k0 < g.K; k0 += kBK) {
-        stage_operand<BM, NT>(As, g.A, g.sam, g.sak, g.M, g.K, m0, k0, g.a_mode, tid);
-        stage_operand<BN, NT>(Bs, g.B, g.sbn, g.sbk, g.N, g.K, n0, k0, g.b_mode, tid);
-        __syncthreads();
-        bf16x8 a[TI], b[TJ];
+    auto multiply = [&](const uint16_t* la, const uint16_t* lb, int kk) {
+        bf16x8 af[TI], bf[TJ];
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
-            a[i] = *reinterpret_cast<const bf16x8*>(&As[(wm + 16 * i + fr) * kLdsK + fk]);
+        for (int i = 0; i < TI; ++i) af[i] = OpA::fragment(la, wm + 16 * i, kk, lane);
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
-            b[j] = *reinterpret_cast<const bf16x8*>(&Bs[(wn + 16 * j + fr) * kLdsK + fk]);
+        for (int j = 0; j < TJ; ++j) bf[j] = OpB::fragment(lb, wn + 16 * j, kk, lane);
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
+                acc[i][j] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
+    };
+    int buf = 0;
+    int64_t done = 0;  // k handled by the first loop
+    if (OpA::plain(g.M, m0) && OpB::plain(g.N, n0) && g.K >= BK) {
+        // D steps in flight; loads past the last step repeat it, so that the
+        // loop has no branch around a load (the wait for one would be a wait
+        // for all)
+        Operand<BM, BK, AMODE, D> a;
+        Operand<BN, BK, BMODE, D> b;
+        a.place(g.sam, g.sak, g.M, m0);
+        b.place(g.sbn, g.sbk, g.N, n0);
+        const uint16_t* const A0 = g.A + m0 * g.sam;
+        const uint16_t* const B0 = g.B + n0 * g.sbn;
+        done = g.K / BK * BK;
+        const int64_t last = done - BK;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int64_t k = (int64_t)d * BK < last ? (int64_t)d * BK : last;
+            a.fetch(d, A0 + k * g.sak);
+            b.fetch(d, B0 + k * g.sbk);
+        }
+        auto step = [&](int d, int64_t k0) {
+            uint16_t* const la = As + buf * OpA::kLds;
+            uint16_t* const lb = Bs + buf * OpB::kLds;
+            a.put(d, la);
+            b.put(d, lb);
+            __syncthreads();
+            const int64_t k = k0 + D * BK < last ? k0 + D * BK : last;
+            a.fetch(d, A0 + k * g.sak);
+            b.fetch(d, B0 + k * g.sbk);
+            // the loads stay here, ahead of this step's products
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += 32) multiply(la, lb, kk);
+            buf ^= 1;
+        };
+        int64_t k0 = 0;
+        for (; k0 + (D - 1) * BK < done; k0 += D * BK)
+#pragma unroll
+            for (int d = 0; d < D; ++d) step(d, k0 + d * BK);
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (k0 + d * BK < done) step(d, k0 + d * BK);
     }
+    for (int64_t k0 = done; k0 < g.K; k0 += BK) {
+        OpA a;
+        OpB b;
+        uint16_t* const la = As + buf * OpA::kLds;
+        uint16_t* const lb = Bs + buf * OpB::kLds;
+        a.fetch_edge(g.A, g.sam, g.sak, g.M, g.K, m0, k0);
+        b.fetch_edge(g.B, g.sbn, g.sbk, g.N, g.K, n0, k0);
+        a.put(0, la);
+        b.put(0, lb);
+        __syncthreads();
+#pragma unroll 1
+        for (int kk = 0; kk < BK && k0 + kk < g.K; kk += 32) multiply(la, lb, kk);
+        buf ^= 1;
+    }
+    // All of the epilogue's loads come before its first store: a wait for a
+    // load also waits for the stores issued before it.
+    const int64_t m = m0 + wm + (lane & 15), n = n0 + wn + 4 * (lane >> 4);
+    if (m0 + BM <= g.M && n0 + BN <= g.N && g.c_vec) {
+        gemm_epilogue<TI, TJ, true>(g, m, n, acc);
+    } else {
+        gemm_epilogue<TI, TJ, false>(g, m, n, acc);
+    }
+}
 
+// Column sums of an n x c FP32 matrix, 16 columns per workgroup of 256 threads
+// and 16 row phases (row i goes to phase i mod 16): each thread sums its phase
+// in row order and the 16 phase sums are added in phase order, so the result
+// does not depend on scheduling.
+struct ColSums {
+    const float* x;
+    int64_t n;
+    int32_t c;
+    int32_t pad;
+    float* out;
+};
+
+constexpr int kSumCols = 16, kSumPhases = 16;
+
+__device__ __forceinline__ void col_sums_block(const ColSums& S, int64_t block, float* lds) {
+    const int tx = threadIdx.x % kSumCols, ph = threadIdx.x / kSumCols;
+    const int64_t j = block * kSumCols + tx;
+    float s = 0.f;
+    if (j < S.c) {
+        int64_t i = ph;
+        // eight rows in flight, added in order
+        for (; i + 7 * kSumPhases < S.n; i += 8 * kSumPhases) {
+            float v[8];
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+            for (int q = 0; q < 8; ++q) v[q] = S.x[(i + q * kSumPhases) * S.c + j];
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-                const int64_t n = n0 + wn + 16 * j + (lane & 15);
-                if (m >= g.M || n >= g.N) continue;
-                float v = acc[i][j][r];
-                if (g.bias) v += g.bias[n];
-                if (g.relu) v = v > 0.f ? v : 0.f;
-                if (g.mask && !(bf16_bits_to_f32(g.mask[m * g.ldc + n]) > 0.f)) v = 0.f;
-                if (g.Cf) g.Cf[m * g.ldc + n] = v;
-                if (g.Cb) g.Cb[m * g.ldc + n] = f32_to_bf16_bits(v);
-            }
+            for (int q = 0; q < 8; ++q) s += v[q];
+        }
+        for (; i < S.n; i += kSumPhases) s += S.x[i * S.c + j];
+    }
+    lds[ph * kSumCols + tx] = s;
+    __syncthreads();
+    if (ph == 0 && j < S.c) {
+        float t = lds[tx];
+        for (int q = 1; q < kSumPhases; ++q) t += lds[q * kSumCols + tx];
+        S.out[j] = t;
+    }
+}
+
+// Up to two independent products and one set of column sums in one launch: the
+// blocks below tiles[0] take the first product's tiles, those below
+// tiles[0] + tiles[1] the second's, the rest the sums.  (A backward layer's
+// weight gradient, input gradient and bias gradient need the same inputs; each
+// alone leaves most of the chip idle.)
+struct GemmGroup {
+    GemmArgs g[2];
+    ColSums s;
+    int64_t tiles[2];
+    int64_t blocks;
+};
+
+// GENERAL: any load modes, else those of the network's products (X.W, dY.W^T
+// and X^T.dY with 16-byte aligned rows).
+template <int BM, int BN, int BK, int WM, int WN, int D, bool GENERAL>
+__global__ __launch_bounds__(256, 2) void gemm_group_kernel(const GemmGroup G) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[gemm_lds<BM, BN, BK>()];
+    int64_t b = linear_block();
+    if (b >= G.blocks) return;
+    if (b >= G.tiles[0] + G.tiles[1]) {
+        col_sums_block(G.s, b - G.tiles[0] - G.tiles[1], reinterpret_cast<float*>(lds));
+        return;
+    }
+    const int which = b >= G.tiles[0];
+    if (which) b -= G.tiles[0];
+    const GemmArgs& g = G.g[which];
+    // neighbouring tiles, which share their rows of A, on one XCD
+    b = xcd_remap(b, G.tiles[which]);
+    const int64_t across = (g.N + BN - 1) / BN;
+    const int64_t tm = b / across, m0 = tm * BM, n0 = (b - tm * across) * BN;
+    if constexpr (GENERAL) {
+        if (g.a_mode == kLoadK && g.b_mode == kLoadScalar)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadK, kLoadScalar>(g, m0, n0, lds);
+        else if (g.a_mode == kLoadRows && g.b_mode == kLoadK)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadRows, kLoadK>(g, m0, n0, lds);
+        else if (g.a_mode == kLoadRows && g.b_mode == kLoadScalar)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadRows, kLoadScalar>(g, m0, n0, lds);
+        else if (g.a_mode == kLoadScalar && g.b_mode == kLoadK)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadScalar, kLoadK>(g, m0, n0, lds);
+        else if (g.a_mode == kLoadScalar && g.b_mode == kLoadRows)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadScalar, kLoadRows>(g, m0, n0, lds);
+        else
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadScalar, kLoadScalar>(g, m0, n0, lds);
+    } else {
+        if (g.a_mode == kLoadRows)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadRows, kLoadRows>(g, m0, n0, lds);
+        else if (g.b_mode == kLoadRows)
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadK, kLoadRows>(g, m0, n0, lds);
+        else
+            gemm_tile<BM, BN, BK, WM, WN, D, kLoadK, kLoadK>(g, m0, n0, lds);
+    }
 }
 
 // One wavefront per row: softmax of the row's logits, cross-entropy against
@@ -249,29 +557,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const lsp_peak* __r
         __syncthreads();
     }
     if (threadIdx.x == 0) *count = (int32_t)done;
-}
-
-// Column sums of an n x c FP32 matrix.  A workgroup covers 64 columns with 16
-// row phases (row i goes to phase i mod 16); each thread sums its phase in row
-// order and the 16 phase sums are added in phase order, so the result does not
-// depend on scheduling.
-constexpr int kSumCols = 64, kSumPhases = 16;
-
-__global__ __launch_bounds__(kSumCols* kSumPhases) void col_sums_kernel(
-    const float* __restrict__ x, int64_t n, int32_t c, float* out) {
-    __shared__ float s_part[kSumPhases][kSumCols];
-    const int tx = threadIdx.x % kSumCols, ph = threadIdx.x / kSumCols;
-    const int32_t j = blockIdx.x * kSumCols + tx;
-    float s = 0.f;
-    if (j < c)
-        for (int64_t i = ph; i < n; i += kSumPhases) s += x[i * c + j];
-    s_part[ph][tx] = s;
-    __syncthreads();
-    if (ph == 0 && j < c) {
-        float t = s_part[0][tx];
-        for (int q = 1; q < kSumPhases; ++q) t += s_part[q][tx];
-        out[j] = t;
-    }
 }
 
 // Column mean and 1/std (population) of an n x d FP32 matrix; a column with no
@@ -438,21 +723,45 @@ __global__ void cast_bf16_kernel(const float* __restrict__ x, int64_t count, uin
 }
 
 // Adam with bias correction on FP32 master parameters; optionally refreshes
-// the BF16 copy the GEMMs read.
-__global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ grad,
-                            float* __restrict__ m, float* __restrict__ v, int64_t count,
-                            float lr, float b1, float b2, float eps, float c1, float c2,
-                            uint16_t* p_bf16) {
-    const int64_t i = linear_block() * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const float gi = grad[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    p[i] = pi;
-    if (p_bf16) p_bf16[i] = f32_to_bf16_bits(pi);
+// the BF16 copy the GEMMs read.  One launch takes up to six parameter arrays,
+// each from a block of its own on.
+struct AdamArray {
+    float* p;
+    const float* grad;
+    float* m;
+    float* v;
+    uint16_t* p_bf16;
+    int64_t count;
+    int64_t first;  // its first block
+};
+
+constexpr int kAdamArrays = 6, kAdamThreads = 256;
+
+struct AdamArgs {
+    AdamArray a[kAdamArrays];
+    int32_t n;
+    float lr, b1, b2, eps, c1, c2;
+    int64_t blocks;
+};
+
+__global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs A) {
+    const int64_t b = linear_block();
+    if (b >= A.blocks) return;
+    int k = 0;
+#pragma unroll
+    for (int q = 1; q < kAdamArrays; ++q)
+        if (q < A.n && b >= A.a[q].first) k = q;
+    const AdamArray& a = A.a[k];
+    const int64_t i = (b - a.first) * kAdamThreads + threadIdx.x;
+    if (i >= a.count) return;
+    const float gi = a.grad[i];
+    const float mi = A.b1 * a.m[i] + (1.f - A.b1) * gi;
+    const float vi = A.b2 * a.v[i] + (1.f - A.b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float pi = a.p[i] - A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + A.eps);
+    a.p[i] = pi;
+    if (a.p_bf16) a.p_bf16[i] = f32_to_bf16_bits(pi);
 }
 
 // One wavefront per row: the k largest of c logits (lowest index on ties), in
@@ -556,18 +865,11 @@ __global__ __launch_bounds__(256) void trim_bands_kernel(
 }  // namespace
 }  // namespace lsp
 
-extern "C" {
-
-lsp_status lsp_gemm_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t sam, int64_t sak,
-                         const void* B, int64_t sbk, int64_t sbn, const float* bias,
-                         const void* mask, int32_t relu, float* C, void* C_bf16, int64_t ldc,
-                         void* stream) {
-    if (M < 0 || N < 0 || K < 0 || (M > 0 && N > 0 && (!A || !B)) || (!C && !C_bf16) ||
-        ldc < N || (relu != 0 && relu != 1))
-        return LSP_EINVAL;
-    if ((M + 63) / 64 > 65535 || (N + 63) / 64 > 65535) return LSP_EUNSUPPORTED;
-    if (M == 0 || N == 0) return LSP_OK;
-    lsp::GemmArgs g;
+static lsp::GemmArgs gemm_args(int64_t M, int64_t N, int64_t K, const void* A, int64_t sam,
+                               int64_t sak, const void* B, int64_t sbk, int64_t sbn,
+                               const float* bias, const void* mask, int32_t relu, float* C,
+                               void* C_bf16, int64_t ldc) {
+    lsp::GemmArgs g = {};
     g.M = M;
     g.N = N;
     g.K = K;
@@ -580,7 +882,6 @@ lsp_status lsp_gemm_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t
     g.bias = bias;
     g.mask = static_cast<const uint16_t*>(mask);
     g.relu = relu;
-    g.pad = 0;
     g.Cf = C;
     g.Cb = static_cast<uint16_t*>(C_bf16);
     g.ldc = ldc;
@@ -588,24 +889,108 @@ lsp_status lsp_gemm_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t
     // every 8-element chunk the tiles read starts on a 16-byte boundary
     auto mode = [](const void* X, int64_t so, int64_t sk) {
         const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
-        if (aligned && sk == 1 && so % 8 == 0) return (int32_t)lsp::kLoadK;
-        if (aligned && so == 1 && sk % 8 == 0) return (int32_t)lsp::kLoadRows;
+        auto fits = [](int64_t st) { return st >= 0 && st % 8 == 0 && st < lsp::kMaxStride; };
+        if (aligned && sk == 1 && fits(so)) return (int32_t)lsp::kLoadK;
+        if (aligned && so == 1 && fits(sk)) return (int32_t)lsp::kLoadRows;
         return (int32_t)lsp::kLoadScalar;
     };
     g.a_mode = mode(A, sam, sak);
     g.b_mode = mode(B, sbn, sbk);
+    g.c_vec = ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15u) == 0 &&
+              (reinterpret_cast<uintptr_t>(C_bf16) & 7u) == 0 &&
+              (reinterpret_cast<uintptr_t>(mask) & 7u) == 0;
+    return g;
+}
+
+// Launches the first n products of G (with G.s where G.s.c > 0) with one tile
+// size: 128 x 128 where it gives two workgroups per CU, 64 x 64 where it gives
+// one for every other CU, else 32 x 32.  Measured (us):
+//   rows x K x columns     128 tiles    64 tiles    32 tiles
+//   20,000 x 1,088 x 512   628:  44   2,504:  52        113
+//   20,000 x 512 x 256     314:  18.6 1,252:  18         34
+//   20,000 x 256 x 64      157:  11     313:   7.2        9
+//   1,088 x 512 x 512                   136:   6.9  544:  8.3
+//   512 x 512 x 256 + 512 x 256 x 512    96:   7.1  384:  6.2
+//   512 x 1,088 x 512                    64:  10.2  256:  9.2
+static lsp_status launch_group(lsp::GemmGroup& G, int n, void* stream) {
+    for (int q = 0; q < n; ++q)
+        if ((G.g[q].M + 63) / 64 > 65535 || (G.g[q].N + 63) / 64 > 65535) return LSP_EUNSUPPORTED;
+    auto count = [&](int64_t t) {
+        int64_t all = 0;
+        for (int q = 0; q < n; ++q) {
+            G.tiles[q] = (G.g[q].M + t - 1) / t * ((G.g[q].N + t - 1) / t);
+            all += G.tiles[q];
+        }
+        return all;
+    };
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    // 128 x 128 tiles (eight waves of 64 x 32) where they still give a few
-    // hundred workgroups, else 64 x 64 (four waves of 32 x 32)
-    if (M >= 128 && N >= 128 && ((M + 127) / 128) * ((N + 127) / 128) >= 256) {
-        const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
-        hipLaunchKernelGGL((lsp::gemm_bf16_kernel<128, 128, 2, 4>), grid, dim3(512), 0, s, g);
-    } else {
-        const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-        hipLaunchKernelGGL((lsp::gemm_bf16_kernel<64, 64, 2, 2>), grid, dim3(lsp::kGemmThreads), 0,
-                           s, g);
+    const int64_t sums = G.s.c > 0 ? (G.s.c + lsp::kSumCols - 1) / lsp::kSumCols : 0;
+    // other load modes (unaligned or strided operands) take the 64 x 64 tile
+    bool general = false;
+    for (int q = 0; q < n; ++q) {
+        const int32_t am = G.g[q].a_mode, bm = G.g[q].b_mode;
+        general |= am == lsp::kLoadScalar || bm == lsp::kLoadScalar ||
+                   (am == lsp::kLoadRows && bm == lsp::kLoadK);
     }
+    if (general && n > 1) {
+        // products of different modes: one launch each, the sums with the last
+        for (int q = 0; q < n; ++q) {
+            lsp::GemmGroup one = {};
+            one.g[0] = G.g[q];
+            if (q + 1 == n) one.s = G.s;
+            const lsp_status st = launch_group(one, 1, stream);
+            if (st != LSP_OK) return st;
+        }
+        return LSP_OK;
+    }
+    const int t = general ? 64 : count(128) >= 512 ? 128 : count(64) >= 128 ? 64 : 32;
+    G.blocks = count(t) + sums;
+    const dim3 grid = lsp::grid_for(G.blocks), threads(256);
+    if (general)
+        hipLaunchKernelGGL((lsp::gemm_group_kernel<64, 64, 64, 2, 2, 1, true>), grid, threads, 0, s, G);
+    else if (t == 128)
+        hipLaunchKernelGGL((lsp::gemm_group_kernel<128, 128, 64, 2, 2, 1, false>), grid, threads, 0, s,
+                           G);
+    else if (t == 64)
+        hipLaunchKernelGGL((lsp::gemm_group_kernel<64, 64, 64, 2, 2, 3, false>), grid, threads, 0, s,
+                           G);
+    else
+        hipLaunchKernelGGL((lsp::gemm_group_kernel<32, 32, 64, 2, 2, 4, false>), grid, threads, 0, s,
+                           G);
     return hipGetLastError() == hipSuccess ? LSP_OK : LSP_EHIP;
+}
+
+// Up to six parameter arrays in one launch; arrays of no elements take none.
+static lsp_status launch_adam(lsp::AdamArgs& A, int32_t step, float beta1, float beta2,
+                              void* stream) {
+    A.c1 = 1.f - powf(beta1, (float)step);
+    A.c2 = 1.f - powf(beta2, (float)step);
+    A.b1 = beta1;
+    A.b2 = beta2;
+    A.blocks = 0;
+    for (int q = 0; q < A.n; ++q) {
+        A.a[q].first = A.blocks;
+        A.blocks += (A.a[q].count + lsp::kAdamThreads - 1) / lsp::kAdamThreads;
+    }
+    hipLaunchKernelGGL(lsp::adam_kernel, lsp::grid_for(A.blocks), dim3(lsp::kAdamThreads), 0,
+                       static_cast<hipStream_t>(stream), A);
+    return hipGetLastError() == hipSuccess ? LSP_OK : LSP_EHIP;
+}
+
+extern "C" {
+
+lsp_status lsp_gemm_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t sam, int64_t sak,
+                         const void* B, int64_t sbk, int64_t sbn, const float* bias,
+                         const void* mask, int32_t relu, float* C, void* C_bf16, int64_t ldc,
+                         void* stream) {
+    if (M < 0 || N < 0 || K < 0 || (M > 0 && N > 0 && (!A || !B)) || (!C && !C_bf16) ||
+        ldc < N || (relu != 0 && relu != 1))
+        return LSP_EINVAL;
+    if ((M + 63) / 64 > 65535 || (N + 63) / 64 > 65535) return LSP_EUNSUPPORTED;
+    if (M == 0 || N == 0) return LSP_OK;
+    lsp::GemmGroup G = {};
+    G.g[0] = gemm_args(M, N, K, A, sam, sak, B, sbk, sbn, bias, mask, relu, C, C_bf16, ldc);
+    return launch_group(G, 1, stream);
 }
 
 lsp_status lsp_softmax_xent(const float* logits, const int32_t* labels, int64_t n, int32_t c,
@@ -621,10 +1006,9 @@ lsp_status lsp_softmax_xent(const float* logits, const int32_t* labels, int64_t 
 
 lsp_status lsp_col_sums(const float* x, int64_t n, int32_t c, float* out, void* stream) {
     if (n < 0 || c < 1 || !out || (n > 0 && !x)) return LSP_EINVAL;
-    hipLaunchKernelGGL(lsp::col_sums_kernel, dim3((c + lsp::kSumCols - 1) / lsp::kSumCols),
-                       dim3(lsp::kSumCols * lsp::kSumPhases), 0, static_cast<hipStream_t>(stream),
-                       x, n, c, out);
-    return hipGetLastError() == hipSuccess ? LSP_OK : LSP_EHIP;
+    lsp::GemmGroup G = {};
+    G.s = lsp::ColSums{x, n, c, 0, out};
+    return launch_group(G, 0, stream);
 }
 
 lsp_status lsp_col_stats(const float* x, int64_t n, int32_t d, float* mean, float* inv_std,
@@ -658,11 +1042,12 @@ lsp_status lsp_adam(float* param, const float* grad, float* m, float* v, int64_t
                     void* stream) {
     if (count < 0 || step < 1 || (count > 0 && (!param || !grad || !m || !v))) return LSP_EINVAL;
     if (count == 0) return LSP_OK;
-    const float c1 = 1.f - powf(beta1, (float)step), c2 = 1.f - powf(beta2, (float)step);
-    hipLaunchKernelGGL(lsp::adam_kernel, lsp::grid_for((count + 255) / 256), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), param, grad, m, v, count, lr, beta1,
-                       beta2, eps, c1, c2, static_cast<uint16_t*>(param_bf16));
-    return hipGetLastError() == hipSuccess ? LSP_OK : LSP_EHIP;
+    lsp::AdamArgs A = {};
+    A.n = 1;
+    A.lr = lr;
+    A.eps = eps;
+    A.a[0] = lsp::AdamArray{param, grad, m, v, static_cast<uint16_t*>(param_bf16), count, 0};
+    return launch_adam(A, step, beta1, beta2, stream);
 }
 
 // ---- the network as a whole: the layer order of lsp_mlp, from the primitives
@@ -736,7 +1121,7 @@ lsp_status lsp_mlp_backward(const lsp_mlp* net, const void* x_bf16, const int32_
         return LSP_EINVAL;
     const MlpScratch sc = mlp_scratch(net, n);
     if (workspace_bytes < sc.total) return LSP_ENOMEM;
-    const int64_t d0 = net->dims[0], d1 = net->dims[1], d2 = net->dims[2], d3 = net->dims[3];
+    const int64_t d3 = net->dims[3];
     char* ws = static_cast<char*>(workspace);
     float* g3 = reinterpret_cast<float*>(ws + sc.off[0]);
     void* g3b = ws + sc.off[1];
@@ -747,27 +1132,23 @@ lsp_status lsp_mlp_backward(const lsp_mlp* net, const void* x_bf16, const int32_
     lsp_status st = lsp_softmax_xent(logits, labels, n, (int32_t)d3, scale, g3, g3b, loss_rows,
                                      stream);
     if (st != LSP_OK) return st;
+    // Each layer's weight gradient, bias gradient and input gradient in one
+    // launch (per call as lsp_gemm_bf16 and lsp_col_sums would compute them).
     // layer 3: dW_2 = h2^T g3, db_2 = column sums of g3, dz2 = (g3 W_2^T) where h2 > 0
-    if ((st = lsp_gemm_bf16(d2, d3, n, h2_bf16, 1, d2, g3b, d3, 1, nullptr, nullptr, 0,
-                            grads->w[2], nullptr, d3, stream)) != LSP_OK)
-        return st;
-    if ((st = lsp_col_sums(g3, n, (int32_t)d3, grads->b[2], stream)) != LSP_OK) return st;
-    if ((st = lsp_gemm_bf16(n, d2, d3, g3b, d3, 1, net->w_bf16[2], 1, d3, nullptr, h2_bf16, 0,
-                            dz2, dz2b, d2, stream)) != LSP_OK)
-        return st;
-    // layer 2
-    if ((st = lsp_gemm_bf16(d1, d2, n, h1_bf16, 1, d1, dz2b, d2, 1, nullptr, nullptr, 0,
-                            grads->w[1], nullptr, d2, stream)) != LSP_OK)
-        return st;
-    if ((st = lsp_col_sums(dz2, n, (int32_t)d2, grads->b[1], stream)) != LSP_OK) return st;
-    if ((st = lsp_gemm_bf16(n, d1, d2, dz2b, d2, 1, net->w_bf16[1], 1, d2, nullptr, h1_bf16, 0,
-                            dz1, dz1b, d1, stream)) != LSP_OK)
-        return st;
-    // layer 1
-    if ((st = lsp_gemm_bf16(d0, d1, n, x_bf16, 1, d0, dz1b, d1, 1, nullptr, nullptr, 0,
-                            grads->w[0], nullptr, d1, stream)) != LSP_OK)
-        return st;
-    return lsp_col_sums(dz1, n, (int32_t)d1, grads->b[0], stream);
+    auto layer = [&](int l, const void* in, const float* g, const void* gb, float* dz, void* dzb) {
+        const int64_t di = net->dims[l], dn = net->dims[l + 1];
+        lsp::GemmGroup G = {};
+        G.g[0] = gemm_args(di, dn, n, in, 1, di, gb, dn, 1, nullptr, nullptr, 0, grads->w[l],
+                           nullptr, dn);
+        if (dz)
+            G.g[1] = gemm_args(n, di, dn, gb, dn, 1, net->w_bf16[l], 1, dn, nullptr, in, 0, dz,
+                               dzb, di);
+        G.s = lsp::ColSums{g, n, (int32_t)dn, 0, grads->b[l]};
+        return launch_group(G, dz ? 2 : 1, stream);
+    };
+    if ((st = layer(2, h2_bf16, g3, g3b, dz2, dz2b)) != LSP_OK) return st;
+    if ((st = layer(1, h1_bf16, dz2, dz2b, dz1, dz1b)) != LSP_OK) return st;
+    return layer(0, x_bf16, dz1, dz1b, nullptr, nullptr);
 }
 
 lsp_status lsp_mlp_adam(const lsp_mlp* net, const lsp_mlp_grads* grads, const lsp_mlp_grads* m,
@@ -775,16 +1156,18 @@ lsp_status lsp_mlp_adam(const lsp_mlp* net, const lsp_mlp_grads* grads, const ls
                         float eps, void* stream) {
     if (!mlp_ok(net) || !grads_ok(grads) || !grads_ok(m) || !grads_ok(v) || step < 1)
         return LSP_EINVAL;
+    lsp::AdamArgs A = {};
+    A.n = 6;
+    A.lr = lr;
+    A.eps = eps;
     for (int l = 0; l < 3; ++l) {
         const int64_t nw = (int64_t)net->dims[l] * net->dims[l + 1];
-        lsp_status st = lsp_adam(net->w[l], grads->w[l], m->w[l], v->w[l], nw, step, lr, beta1,
-                                 beta2, eps, net->w_bf16[l], stream);
-        if (st != LSP_OK) return st;
-        st = lsp_adam(net->b[l], grads->b[l], m->b[l], v->b[l], net->dims[l + 1], step, lr,
-                      beta1, beta2, eps, nullptr, stream);
-        if (st != LSP_OK) return st;
+        A.a[2 * l] = lsp::AdamArray{net->w[l], grads->w[l], m->w[l], v->w[l],
+                                    static_cast<uint16_t*>(net->w_bf16[l]), nw, 0};
+        A.a[2 * l + 1] = lsp::AdamArray{net->b[l], grads->b[l], m->b[l], v->b[l], nullptr,
+                                        net->dims[l + 1], 0};
     }
-    return LSP_OK;
+    return launch_adam(A, step, beta1, beta2, stream);
 }
 
 lsp_status lsp_top_k(const float* logits, int64_t n, int32_t c, int32_t k, int32_t* idx,
