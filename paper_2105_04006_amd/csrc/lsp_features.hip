@@ -264,7 +264,8 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
                     const int sl = unit >> 2, pair = unit & 3;
                     const int j = c0 + sl * kSlice + 8 * half + 2 * pair;
                     h2 v[8];
-                    gen_b2(v, hb, s_tau + j, b - j);
+                    gen_b2(v, hb, s_tau + j);
+                    if (left < (sl + 1) * kSlice) trim_b2(v, b - j);
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
                         reinterpret_cast<h2*>(&s_b[buf][sl][k][lane])[pair] = v[k];

@@ -29,6 +29,15 @@
 // for every block of an object, so a workgroup's waves make a quarter each and
 // share them through LDS.
 //
+// What bounds it: the card's power.  With all slices' operands in registers and
+// nothing but these matrix instructions the clock falls to 1.6 GHz (a large
+// FP16 library product reaches 1.09 PFLOP/s); a long object's slice takes
+// 0.74 us per SIMD, the same rate.  Taken without gain for that reason: fewer
+// vector instructions for the factors (-13 %), the next slice's factors made
+// between the matrix instructions, eight waves sharing the offset factors.
+// Around the slices a tile costs 2.7 us per SIMD (staging, first factors, the
+// powers of its bins).
+//
 // Measured, vector kernels -> here: 2,500 objects of 20..500 points on 250,000
 // bins 19.6 -> 4.3 ms (8.3e12 -> 3.8e13 (observation, bin) pairs a second);
 // 4,096 points on 500,000 bins 295 -> 76 us; error against 64 bits 1e-6 -> 2e-7.
@@ -55,13 +64,12 @@ constexpr int kFix = kMxTile;                 // bins per fix-up tile
 __device__ __forceinline__ void split2(float x, float y, h2& hi, h2& lo) {
     hi = __builtin_convertvector((f2){x, y}, h2);
     const float m1 = -1.0f;
-    float lx, ly;
-    // x - hi in one instruction each (a mixed-precision fused multiply-add)
-    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(lx) : "v"(hi), "v"(m1), "v"(x));
-    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
-        : "=v"(ly)
+    // f16(x - hi) in one instruction each (a mixed-precision fused multiply-add
+    // into the low, then the high half; x - hi is exact, so it rounds once)
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(m1), "v"(x));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+        : "+v"(lo)
         : "v"(hi), "v"(m1), "v"(y));
-    lo = __builtin_convertvector((f2){lx, ly}, h2);
 }
 
 __device__ __forceinline__ void put2(h8& v, int p, h2 x) {
@@ -107,29 +115,46 @@ __device__ __forceinline__ void gen_a(Frag& F, double f, const double* tau, cons
 }
 
 // The offset factors of two observations, as pairs: hi halves v[0..3], lo v[4..7].
-__device__ __forceinline__ void gen_b2(h2 (&v)[8], double h, const double* tau, int valid) {
+__device__ __forceinline__ void gen_b2(h2 (&v)[8], double h, const double* tau) {
     float s0, c0, s1, c1;
     sincos_rev(h, tau[0], s0, c0);
     sincos_rev(h, tau[1], s1, c1);
-    const float w0 = 0 < valid ? 1.0f : 0.0f, w1 = 1 < valid ? 1.0f : 0.0f;
-    c0 *= w0;
-    s0 *= w0;
-    c1 *= w1;
-    s1 *= w1;
     split2(c0, c1, v[0], v[4]);
     split2(s0, s1, v[1], v[5]);
-    split2(fmaf(c0, c0, -0.5f * w0), fmaf(c1, c1, -0.5f * w1), v[2], v[6]);
+    split2(fmaf(c0, c0, -0.5f), fmaf(c1, c1, -0.5f), v[2], v[6]);
     split2(c0 * s0, c1 * s1, v[3], v[7]);
 }
 
-// B side: observations from `valid` on are padding and get zero factors.
-__device__ __forceinline__ void gen_b(Frag& F, double h, const double* tau, int valid) {
+// Zero factors for the observations from `valid` on: the padding of an
+// object's last slice.  (Only that slice is trimmed: a mask on every factor
+// cost a sixth of the factors' instructions.)
+__device__ __forceinline__ void trim_b2(h2 (&v)[8], int valid) {
+    const uint32_t keep = valid >= 2 ? ~0u : valid == 1 ? 0xFFFFu : 0u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        v[q] = __builtin_bit_cast(h2, __builtin_bit_cast(uint32_t, v[q]) & keep);
+}
+
+// B side.  The caller trims the slice that holds padding.
+__device__ __forceinline__ void gen_b(Frag& F, double h, const double* tau) {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         h2 v[8];
-        gen_b2(v, h, tau + 2 * p, valid - 2 * p);
+        gen_b2(v, h, tau + 2 * p);
 #pragma unroll
         for (int q = 0; q < 8; ++q) put2(F.q[q], p, v[q]);
+    }
+}
+
+__device__ __forceinline__ void trim_b(Frag& F, int valid) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        u4 v = __builtin_bit_cast(u4, F.q[q]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            v[p] &= valid >= 2 * p + 2 ? ~0u : valid == 2 * p + 1 ? 0xFFFFu : 0u;
+        F.q[q] = __builtin_bit_cast(h8, v);
     }
 }
 

@@ -3,65 +3,101 @@
 // whose waves split the observations.
 #include "lsp_mx.h"
 
+#include <type_traits>
+
 namespace lsp {
 namespace {
 
 using namespace mx;
 
-// The best bin of a lane: larger power first; bins are offered in increasing
-// index, so a strict comparison keeps the lowest of equals.
+// The end of a tile: a wave holds the sums of its bins in its accumulators,
+// some bins a lane.  All powers are computed first and without a branch, so
+// that their chains (a reciprocal each) overlap; the best is tracked as the
+// number of the lane's bin; a stored periodogram goes out in a pass of its own.
+// (With a bounds check and a store branch at every bin this took 6.8 us per
+// wave, a quarter of the time of a tile of 260 observations.)
 struct LaneBest {
-    float p;
-    uint32_t i;
+    float p = -1.0f;
+    int bin = 0;  // from the tile's first
+
+    // Bins are offered in increasing order, so a strict comparison keeps the
+    // lowest of equals.
+    __device__ __forceinline__ void offer(float v, int b) {
+        const bool more = v > p;
+        p = more ? v : p;
+        bin = more ? b : bin;
+    }
 };
 
-__device__ __forceinline__ unsigned long long lane_key(const LaneBest& b) {
-    return b.p >= 0.0f ? ((unsigned long long)__float_as_uint(b.p > 0.0f ? b.p : 0.0f) << 32) |
-                             (uint32_t)(0xFFFFFFFFu - b.i)
-                       : 0ull;
+// Key of the wave's best bin (0 where no lane has one): larger power first,
+// then the lower index; w0 is the tile's first bin.
+__device__ __forceinline__ unsigned long long wave_key(const LaneBest& b, int64_t w0) {
+    float m = b.p;
+    auto up = [&](auto ctrl) {
+        const int v = __builtin_amdgcn_update_dpp(__float_as_int(-1.0f), __float_as_int(m),
+                                                  decltype(ctrl)::value, 0xF, 0xF, false);
+        m = fmaxf(m, __int_as_float(v));
+    };
+    // maximum over each row of 16 lanes into its last, then over the rows
+    up(std::integral_constant<int, 0x111>{});  // row_shr:1
+    up(std::integral_constant<int, 0x112>{});  // row_shr:2
+    up(std::integral_constant<int, 0x114>{});  // row_shr:4
+    up(std::integral_constant<int, 0x118>{});  // row_shr:8
+    up(std::integral_constant<int, 0x142>{});  // row_bcast:15
+    up(std::integral_constant<int, 0x143>{});  // row_bcast:31
+    const float top = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), kWave - 1));
+    if (!(top >= 0.0f)) return 0ull;
+    int least = 0x7FFFFFFF;
+    for (unsigned long long ties = __ballot(b.p == top); ties; ties &= ties - 1) {
+        const int bin = __builtin_amdgcn_readlane(b.bin, (int)__builtin_ctzll(ties));
+        least = bin < least ? bin : least;
+    }
+    return ((unsigned long long)__float_as_uint(top > 0.0f ? top : 0.0f) << 32) |
+           (uint32_t)(0xFFFFFFFFu - (uint32_t)(w0 + least));
 }
 
 struct Finish {
     float n4, scale4;
-    int64_t f_lo, f_hi;  // the row's bins
-    int64_t out;         // first periodogram element of the object
-    void* pgram;
+    void* pgram;   // periodogram at the object's first bin, or NULL
     int32_t f64;
+    int left;      // the row's bins from the tile's first, at most a tile
+
+    __device__ __forceinline__ void store(int64_t w0, int bin, float p) const {
+        if (bin >= left) return;
+        if (f64)
+            static_cast<double*>(pgram)[w0 + bin] = (double)p;
+        else
+            static_cast<float*>(pgram)[w0 + bin] = p;
+    }
 };
 
-// Both bins of (block row a, offset m) from their eight sums; i0 is the
-// block's first bin.
-__device__ __forceinline__ void finish_pair(const Finish& R, const float (&v)[8], int64_t i0, int m,
-                                            LaneBest& best, bool& ill) {
-    const int64_t im = i0 + (kOffs - 1 - m), ip = i0 + (kOffs + m);
-    bool i_m, i_p;
-    const float pm = power_mx(v[0] + v[1], v[2] - v[3], v[4] + v[5], v[6] - v[7], R.n4, R.scale4,
-                              i_m);
-    const float pp = power_mx(v[0] - v[1], v[2] + v[3], v[4] - v[5], v[6] + v[7], R.n4, R.scale4,
-                              i_p);
-    if (im < R.f_hi) {
-        ill |= i_m;
-        if (R.pgram) store_pgram(R.pgram, R.f64, R.out + im, (double)pm);
-        if (pm > best.p) best = LaneBest{pm, (uint32_t)im};
-    }
-    if (ip < R.f_hi) {
-        ill |= i_p;
-        if (R.pgram) store_pgram(R.pgram, R.f64, R.out + ip, (double)pp);
-        if (pp > best.p) best = LaneBest{pp, (uint32_t)ip};
-    }
+__device__ __forceinline__ void* object_pgram(const MainParams& P, int64_t obj) {
+    if (!P.pgram) return nullptr;
+    return P.pgram_f64 ? static_cast<void*>(static_cast<double*>(P.pgram) + obj * P.n_f)
+                       : static_cast<void*>(static_cast<float*>(P.pgram) + obj * P.n_f);
+}
+
+// Both bins (0: minus, 1: plus the offset) of a block's offset from their eight sums.
+__device__ __forceinline__ void pair_power(const Finish& R, const float (&v)[8], float (&p)[2],
+                                           bool (&ill)[2]) {
+    p[0] = power_mx(v[0] + v[1], v[2] - v[3], v[4] + v[5], v[6] - v[7], R.n4, R.scale4, ill[0]);
+    p[1] = power_mx(v[0] - v[1], v[2] + v[3], v[4] - v[5], v[6] + v[7], R.n4, R.scale4, ill[1]);
+}
+
+// Bin of (block a, offset m, side) from the tile's first.
+__device__ __forceinline__ int tile_bin(int a, int m, int side) {
+    return a * kBlk + (side ? kOffs + m : kOffs - 1 - m);
 }
 
 __device__ __forceinline__ Finish make_finish(const MainParams& P, const ObjMeta& m,
-                                              const RowRange& rr) {
+                                              const RowRange& rr, int64_t w0) {
     Finish R;
     const double back = ldexp(1.0, -mx_exp_y(m));
     R.n4 = 0.25f * (float)m.n;
     R.scale4 = (float)(0.25 * (m.scale * back * back));
-    R.f_lo = rr.f_lo;
-    R.f_hi = rr.f_hi;
-    R.out = rr.obj * P.n_f;
-    R.pgram = P.pgram;
+    R.pgram = object_pgram(P, rr.obj);
     R.f64 = P.pgram_f64;
+    R.left = (int)(rr.f_hi - w0 < kWaveBins ? rr.f_hi - w0 : kWaveBins);
     return R;
 }
 
@@ -73,6 +109,52 @@ __device__ __forceinline__ void fill_bins(const MainParams& P, const RowRange& r
     if (hi > rr.f_hi) hi = rr.f_hi;
     for (int64_t i = lo + threadIdx.x; i < hi; i += threads)
         store_pgram(P.pgram, P.pgram_f64, rr.obj * P.n_f + i, v);
+}
+
+// A wave's whole tile from its accumulators: stores and marks what has to be,
+// and returns the key of the best bin.  WHOLE: all of its bins are the row's.
+template <bool WHOLE>
+__device__ __forceinline__ unsigned long long finish_wave(const MainParams& P, const Finish& R,
+                                                          const f16v (&acc)[8], int64_t row,
+                                                          int64_t w0, int64_t f_lo, int lane) {
+    const int sub = lane & 31, half = lane >> 5;
+    float p[16][2];
+    unsigned long long best = 0ull;
+#pragma unroll
+    for (int t = 0; t < kWaveBins / kFix; ++t) {
+        LaneBest lb;
+        bool ill = false;
+#pragma unroll
+        for (int r = 8 * t; r < 8 * t + 8; ++r) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = acc[q][r];
+            bool bad[2];
+            pair_power(R, v, p[r], bad);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int a = 8 * (r / 4) + 4 * half + (r & 3);
+                const bool in = WHOLE || tile_bin(a, sub, e) < R.left;
+                ill |= bad[e] & in;
+                lb.offer(in ? p[r][e] : -1.0f, 2 * r + e);
+            }
+        }
+        if (__any(ill)) {
+            const int64_t tile = row * P.tiles_per_row + (w0 - f_lo) / kFix + t;
+            if (lane == 0) atomicOr(&P.ill_bits[tile >> 5], 1u << (tile & 31));
+        } else {
+            const int r = lb.bin >> 1;
+            lb.bin = tile_bin(8 * (r >> 2) + 4 * half + (r & 3), sub, lb.bin & 1);
+            best = umax64(best, wave_key(lb, w0));
+        }
+    }
+    if (R.pgram)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                R.store(w0, tile_bin(8 * (r / 4) + 4 * half + (r & 3), sub, e), p[r][e]);
+    return best;
 }
 
 // W waves per workgroup, each with its own 32 x 32 tile (W consecutive runs of
@@ -129,12 +211,14 @@ __global__ __launch_bounds__(kWave* W, 2) void mx_tile_kernel(const MainParams P
             if (mine < slices) {
                 Frag B;
                 const int j = mine * kSlice + half * 8;
-                gen_b(B, hb, s_tau + j, cnt - j);
+                gen_b(B, hb, s_tau + j);
+                if (cnt < (mine + 1) * kSlice) trim_b(B, cnt - j);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) s_b[buf][wave][q][lane] = B.q[q];
             }
             __syncthreads();
-            const int todo = slices - s0 < W ? slices - s0 : W;
+            // (a wave past the row's end only makes its share of the factors)
+            const int todo = w0 >= rr.f_hi ? 0 : slices - s0 < W ? slices - s0 : W;
             for (int s = 0; s < todo; ++s) {
                 Frag A, B;
                 const int j = (s0 + s) * kSlice + half * 8;
@@ -147,28 +231,11 @@ __global__ __launch_bounds__(kWave* W, 2) void mx_tile_kernel(const MainParams P
         }
     }
 
-    const Finish R = make_finish(P, m, rr);
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int t = 0; t < kWaveBins / kFix; ++t) {
-        LaneBest lb{-1.0f, 0u};
-        bool ill = false;
-#pragma unroll
-        for (int r = 8 * t; r < 8 * t + 8; ++r) {
-            const int a = 8 * (r / 4) + 4 * half + (r & 3);
-            float v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = acc[q][r];
-            finish_pair(R, v, w0 + (int64_t)a * kBlk, sub, lb, ill);
-        }
-        if (__any(ill)) {
-            const int64_t tile = row * P.tiles_per_row + (w0 - rr.f_lo) / kFix + t;
-            if (lane == 0) atomicOr(&P.ill_bits[tile >> 5], 1u << (tile & 31));
-        } else {
-            best = umax64(best, lane_key(lb));
-        }
-    }
-    best = wave_max_u64(best);
+    const Finish R = make_finish(P, m, rr, w0);
+    if (R.left <= 0) return;
+    const unsigned long long best = R.left == kWaveBins
+                                        ? finish_wave<true>(P, R, acc, row, w0, rr.f_lo, lane)
+                                        : finish_wave<false>(P, R, acc, row, w0, rr.f_lo, lane);
     if (lane == 0 && best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
 }
 
@@ -225,7 +292,8 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
         for (int s = uniform_i32(wave); s < slices; s += kSplitW) {
             Frag A, B;
             const int j = s * kSlice + half * 8;
-            gen_b(B, hb, s_tau + j, cnt - j);
+            gen_b(B, hb, s_tau + j);
+            if (cnt < (s + 1) * kSlice) trim_b(B, cnt - j);
             gen_a(A, fa, s_tau + j, s_u + j);
             accumulate(acc, A, B);
         }
@@ -247,9 +315,10 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
         }
     }
 
-    const Finish R = make_finish(P, m, rr);
-    LaneBest lb{-1.0f, 0u};
+    const Finish R = make_finish(P, m, rr, w0);
+    LaneBest lb;
     bool ill = false;
+    float p[2][2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         const int r = 2 * wave + e;
@@ -257,9 +326,18 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
         float v[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q] = sum[q][e];
-        finish_pair(R, v, w0 + (int64_t)a * kBlk, sub, lb, ill);
+        bool bad[2];
+        pair_power(R, v, p[e], bad);
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int bin = tile_bin(a, sub, side);
+            const bool in = bin < R.left;
+            ill |= bad[side] & in;
+            lb.offer(in ? p[e][side] : -1.0f, bin);
+            if (R.pgram) R.store(w0, bin, p[e][side]);
+        }
     }
-    const unsigned long long key = wave_max_u64(lane_key(lb));
+    const unsigned long long key = wave_key(lb, w0);
     const bool any = __any(ill);
     if (lane == 0) {
         s_key[wave] = key;
@@ -377,40 +455,29 @@ __device__ __forceinline__ float power_mx_gen(float c1, float s1, float yc, floa
 
 struct FinishG {
     float n, rn, scale;
-    int64_t f_hi, out;
-    void* pgram;
-    int32_t f64;
+    Finish out;
 };
 
 __device__ __forceinline__ FinishG make_finish_g(const MainParams& P, const ObjMeta& m,
-                                                 const RowRange& rr) {
+                                                 const RowRange& rr, int64_t w0) {
     FinishG R;
     const double up_w = ldexp(1.0, mx_exp_w(m)), back = ldexp(1.0, -mx_exp_y(m));
     R.n = (float)((double)m.n * up_w);
     R.rn = (float)(1.0 / ((double)m.n * up_w));
     R.scale = (float)(m.scale * back * back * up_w);
-    R.f_hi = rr.f_hi;
-    R.out = rr.obj * P.n_f;
-    R.pgram = P.pgram;
-    R.f64 = P.pgram_f64;
+    R.out.pgram = object_pgram(P, rr.obj);
+    R.out.f64 = P.pgram_f64;
+    R.out.left = (int)(rr.f_hi - w0 < kGBins ? rr.f_hi - w0 : kGBins);
     return R;
 }
 
-// One of the two bins of (block from bin i0, offset m): the centre minus
-// (side 0) or plus (side 1) the offset.
-__device__ __forceinline__ void finish_bin_g(const FinishG& R, const float (&v)[12], int64_t i0,
-                                             int m, int side, LaneBest& best, bool& ill) {
+// One of the two bins of an offset: the centre minus (side 0) or plus (side 1) it.
+__device__ __forceinline__ float bin_power_g(const FinishG& R, const float (&v)[12], int side,
+                                             bool& ill) {
     const float z = side ? 1.0f : -1.0f;
-    const int64_t i = i0 + (side ? kOffs + m : kOffs - 1 - m);
-    bool bad;
-    const float p = power_mx_gen(fmaf(-z, v[1], v[0]), fmaf(z, v[3], v[2]), fmaf(-z, v[5], v[4]),
-                                 fmaf(z, v[7], v[6]), 4.0f * fmaf(-z, v[9], v[8]),
-                                 4.0f * fmaf(z, v[11], v[10]), R.n, R.rn, R.scale, bad);
-    if (i < R.f_hi) {
-        ill |= bad;
-        if (R.pgram) store_pgram(R.pgram, R.f64, R.out + i, (double)p);
-        if (p > best.p) best = LaneBest{p, (uint32_t)i};
-    }
+    return power_mx_gen(fmaf(-z, v[1], v[0]), fmaf(z, v[3], v[2]), fmaf(-z, v[5], v[4]),
+                        fmaf(z, v[7], v[6]), 4.0f * fmaf(-z, v[9], v[8]),
+                        4.0f * fmaf(z, v[11], v[10]), R.n, R.rn, R.scale, ill);
 }
 
 // Stage observations [jt, jt + cnt) of the object, padded with zeros to whole slices.
@@ -428,32 +495,47 @@ __device__ __forceinline__ void stage_g(const MainParams& P, const ObjMeta& m, i
 }
 
 // Finish one wave's 1,024 bins from complete sums acc[offset half][12].
+template <bool WHOLE>
 __device__ __forceinline__ void finish_tile_g(const MainParams& P, const FinishG& R, int64_t row,
                                               int64_t tile, int64_t w0, const f4v (&acc)[2][12],
                                               int lane) {
-    LaneBest lb{-1.0f, 0u};
+    LaneBest lb;
     bool ill = false;
+    float p[4][4];
+    // in increasing bins of the lane: minus the larger offset, minus the
+    // smaller, plus the smaller, plus the larger
+    auto bin_of = [&](int r, int e) {
+        const int h = e == 0 || e == 3;
+        return tile_bin(4 * (lane >> 4) + r, 16 * h + (lane & 15), e >= 2);
+    };
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int a = 4 * (lane >> 4) + r;
-        // in increasing bins of the lane: minus the larger offset, minus the
-        // smaller, plus the smaller, plus the larger
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int h = e == 0 || e == 3;
             float v[12];
 #pragma unroll
             for (int q = 0; q < 12; ++q) v[q] = acc[h][q][r];
-            finish_bin_g(R, v, w0 + (int64_t)a * kBlk, 16 * h + (lane & 15), e >= 2, lb, ill);
+            bool bad;
+            p[r][e] = bin_power_g(R, v, e >= 2, bad);
+            const bool in = WHOLE || bin_of(r, e) < R.out.left;
+            ill |= bad & in;
+            lb.offer(in ? p[r][e] : -1.0f, 4 * r + e);
         }
     }
     if (__any(ill)) {
         const int64_t bit = row * P.tiles_per_row + tile;
         if (lane == 0) atomicOr(&P.ill_bits[bit >> 5], 1u << (bit & 31));
     } else {
-        const unsigned long long best = wave_max_u64(lane_key(lb));
+        lb.bin = bin_of(lb.bin >> 2, lb.bin & 3);
+        const unsigned long long best = wave_key(lb, w0);
         if (lane == 0 && best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
     }
+    if (R.out.pgram)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) R.out.store(w0, bin_of(r, e), p[r][e]);
 }
 
 // Four waves, each with its own tile; the offset factors of two slices at a
@@ -507,7 +589,7 @@ __global__ __launch_bounds__(kWave* kGW, 2) void mx_gen_tile_kernel(const MainPa
             if (mine < slices) {
                 Frag B;
                 const int j = mine * kGSlice + quarter * 8;
-                gen_b(B, hb, s_tau + j, cnt - j);
+                gen_b(B, hb, s_tau + j);  // (padding has no weight: nothing to trim)
 #pragma unroll
                 for (int q = 0; q < 8; ++q) s_b[buf][wave >> 1][wave & 1][q][lane] = B.q[q];
             }
@@ -528,7 +610,13 @@ __global__ __launch_bounds__(kWave* kGW, 2) void mx_gen_tile_kernel(const MainPa
             buf ^= 1;
         }
     }
-    finish_tile_g(P, make_finish_g(P, m, rr), row, (w0 - rr.f_lo) / kFix, w0, acc, lane);
+    const FinishG R = make_finish_g(P, m, rr, w0);
+    if (R.out.left <= 0) return;
+    const int64_t tile = (w0 - rr.f_lo) / kFix;
+    if (R.out.left == kGBins)
+        finish_tile_g<true>(P, R, row, tile, w0, acc, lane);
+    else
+        finish_tile_g<false>(P, R, row, tile, w0, acc, lane);
 }
 
 // One tile per workgroup, the observations shared out over its eight waves and
@@ -584,7 +672,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 Frag B;
-                gen_b(B, hb * ((double)(16 * h + sub) + 0.5), s_tau + j, cnt - j);
+                gen_b(B, hb * ((double)(16 * h + sub) + 0.5), s_tau + j);
                 accumulate_g(acc[h], A, B);
             }
         }
@@ -604,14 +692,20 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
         sum[q] = v;
     }
     // wave w: accumulator row w / 2 of the lane's four, offset half w % 2
-    const FinishG R = make_finish_g(P, m, rr);
-    LaneBest lb{-1.0f, 0u};
+    const FinishG R = make_finish_g(P, m, rr, w0);
+    LaneBest lb;
     bool ill = false;
-    const int64_t i0 = w0 + (int64_t)(4 * quarter + (wave >> 1)) * kBlk;
 #pragma unroll
-    for (int side = 0; side < 2; ++side)
-        finish_bin_g(R, sum, i0, 16 * (wave & 1) + sub, side, lb, ill);
-    const unsigned long long key = wave_max_u64(lane_key(lb));
+    for (int side = 0; side < 2; ++side) {
+        bool bad;
+        const float p = bin_power_g(R, sum, side, bad);
+        const int bin = tile_bin(4 * quarter + (wave >> 1), 16 * (wave & 1) + sub, side);
+        const bool in = bin < R.out.left;
+        ill |= bad & in;
+        lb.offer(in ? p : -1.0f, bin);
+        if (R.out.pgram) R.out.store(w0, bin, p);
+    }
+    const unsigned long long key = wave_key(lb, w0);
     const bool any = __any(ill);
     if (lane == 0) {
         s_key[wave] = key;
