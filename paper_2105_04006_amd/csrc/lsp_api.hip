@@ -453,6 +453,15 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
     pp.meta = at<ObjMeta>(ws, L.meta);
     pp.dy = method.dy;
     pp.gen = method.gen;
+    // Group keys, flag bits and counters are cleared by the statistics kernel
+    // (up to 16 words a thread; one long series with many rows has more), else
+    // by one of their own.  (Never by a memset: captured graphs replay both.)
+    pp.zero = at<uint32_t>(ws, c.keys ? L.keys : L.queue);
+    pp.zero_words = c.keys ? (int64_t)L.zero_words : kXcds;
+    if (pp.zero_words > 16 * (int64_t)kPrepThreads * n_obj) {
+        if (launch_fill_u32(pp.zero, pp.zero_words, 0u, s) != hipSuccess) return LSP_EHIP;
+        pp.zero_words = 0;
+    }
     if (launch_prep(pp, s) != hipSuccess) return LSP_EHIP;
 
     MainParams mp;
@@ -494,15 +503,6 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
             return LSP_EHIP;
     }
 
-    // key mode: clear keys, flag bits and queue counters in one fill kernel
-    // (a kernel, not a memset node, so that captured graphs replay it safely)
-    if (c.keys) {
-        if (launch_fill_u32(at<unsigned int>(ws, L.keys), (int64_t)L.zero_words, 0u, s) !=
-            hipSuccess)
-            return LSP_EHIP;
-    } else if (f32 && c.persistent && launch_fill_u32(mp.queue, kXcds, 0u, s) != hipSuccess) {
-        return LSP_EHIP;
-    }
     if (c.lpt) {
         OrderParams op;
         op.offsets = offsets;
@@ -519,10 +519,28 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
         mp.row_perm = op.perm;
         mp.n_work = op.total + (kOrderBuckets - 1);
     }
+    PeakParams kp = {};
+    kp.meta = mp.meta;
+    kp.rec = mp.rec;
+    kp.keys = mp.keys;
+    kp.n_obj = n_obj;
+    kp.n_groups = n_groups;
+    kp.row_obj = rows.row_obj;
+    kp.rows_per_group = rows.rows_per_group;
+    kp.rec_per_obj = c.rec_per_group;
+    kp.f_min = grid->f_min;
+    kp.df = df;
+    kp.unit = grid->unit;
+    kp.peaks = peaks;
+    // (the matrix-core kernels take no work from the queue: its first word counts)
+    kp.done = mp.queue;
+    const PeakParams no_peaks = {};
+    bool written = false;  // the peaks, by the kernel before
     if (t_main_begin && hipEventRecord(t_main_begin, s) != hipSuccess) return LSP_EHIP;
     if (c.mx != kMxOff) {
         const bool split = c.mx == kMxSplit;
-        if ((f32 ? launch_mx(mp, c.mx_waves, split, s) : launch_fx(mp, c.mx_waves, split, s)) != hipSuccess)
+        if ((f32 ? launch_mx(mp, c.mx_waves, split, s) : launch_fx(mp, c.mx_waves, split, s)) !=
+            hipSuccess)
             return LSP_EHIP;
     } else if (method.gen) {
         if ((f32 ? launch_gen_fp32p(mp, c.k, c.waves, s) : launch_gen_fp64(mp, c.k, c.waves, s)) !=
@@ -562,7 +580,8 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
             fp.rec = mp.rec;
             fp.dy = method.dy;
             fp.gen = method.gen;
-            if (launch_fixup(fp, s) != hipSuccess) return LSP_EHIP;
+            written = peaks && c.mx != kMxOff && fixup_writes_peaks(fp, kp);
+            if (launch_fixup(fp, written ? kp : no_peaks, s) != hipSuccess) return LSP_EHIP;
         } else {
             CombineParams cp;
             cp.meta = mp.meta;
@@ -583,24 +602,7 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
         }
     }
 
-    if (peaks) {
-        PeakParams kp;
-        kp.meta = mp.meta;
-        kp.rec = mp.rec;
-        kp.keys = mp.keys;
-        kp.n_obj = n_obj;
-        kp.n_groups = n_groups;
-        kp.row_obj = rows.row_obj;
-        kp.rows_per_group = rows.rows_per_group;
-        kp.pad2 = 0;
-        kp.rec_per_obj = c.rec_per_group;
-        kp.f_min = grid->f_min;
-        kp.df = df;
-        kp.unit = grid->unit;
-        kp.pad = 0;
-        kp.peaks = peaks;
-        if (launch_peaks(kp, s) != hipSuccess) return LSP_EHIP;
-    }
+    if (peaks && !written && launch_peaks(kp, s) != hipSuccess) return LSP_EHIP;
     return LSP_OK;
 }
 

@@ -562,6 +562,8 @@ struct PrepParams {
     ObjMeta* meta;
     const double* dy = nullptr;  // generalized form: errors (NULL: unit errors)
     int32_t gen = 0;             // generalized form: weights and a floating mean
+    uint32_t* zero = nullptr;    // words of the scratch memory to clear, for the kernels after
+    int64_t zero_words = 0;
 };
 
 struct MainParams {
@@ -658,6 +660,7 @@ struct PeakParams {
     int32_t unit;
     int32_t pad;
     lsp_peak* peaks;
+    uint32_t* done;          // zeroed counter of the workgroups that have ended (last_workgroup)
 };
 
 hipError_t launch_prep(const PrepParams& p, hipStream_t s);
@@ -679,7 +682,10 @@ hipError_t launch_gen_fp64(const MainParams& p, int kf, int waves, hipStream_t s
 // or, with `split`, one tile whose observations 4 or 8 waves share.
 int64_t fx_item_bins(int waves, bool split);
 hipError_t launch_fx(const MainParams& p, int waves, bool split, hipStream_t s);
-hipError_t launch_fixup(const FixupParams& p, hipStream_t s);
+// k: the call's peaks where the fix-up writes them (fixup_writes_peaks), else
+// with peaks NULL.
+hipError_t launch_fixup(const FixupParams& p, const PeakParams& k, hipStream_t s);
+bool fixup_writes_peaks(const FixupParams& p, const PeakParams& k);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_peaks(const PeakParams& p, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* dst, int64_t n, unsigned int v, hipStream_t s);

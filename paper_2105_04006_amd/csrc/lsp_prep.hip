@@ -86,6 +86,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
     const int64_t o = linear_block();
     const int tid = threadIdx.x;
     if (o >= P.n_obj) return;
+    for (int64_t i = o * kPrepThreads + tid; i < P.zero_words; i += P.n_obj * kPrepThreads)
+        P.zero[i] = 0u;
 
     int64_t j0 = 0, j1 = P.n_obs;
     if (P.offsets) {

@@ -8,41 +8,19 @@
 // tile has already reduced its bins to one record; one workgroup per object
 // reduces the object's records with the same (power desc, index asc) order, so
 // the result does not depend on execution order.
-#include "lsp_common.h"
+#include "lsp_peaks.h"
 
 namespace lsp {
 namespace {
 
 constexpr int kPeakThreads = 256;
 
-// The peak record of one object from its best (power, index).
-__device__ __forceinline__ lsp_peak make_peak(const PeakParams& P, const ObjMeta& m, PeakRec b) {
-    lsp_peak pk;
-    pk.status = m.status;
-    pk.reserved = 0;
-    if (m.status == LSP_OBJ_OK && b.i >= 0) {
-        const double f = grid_freq(P.f_min, P.df, b.i);
-        pk.index = b.i;
-        pk.freq = f;
-        pk.period = P.unit == LSP_UNIT_ANGULAR ? kTwoPi / f : 1.0 / f;
-        pk.power = b.p;
-    } else {
-        pk.index = -1;
-        pk.freq = __builtin_nan("");
-        pk.period = __builtin_nan("");
-        pk.power = m.status == LSP_OBJ_OK ? __builtin_nan("") : fill_value(m.status);
-    }
-    return pk;
-}
-
 __global__ __launch_bounds__(kPeakThreads) void peaks_kernel(const PeakParams P) {
     __shared__ PeakRec s_red[kPeakThreads / kWave];
     const int64_t grp = linear_block();
     if (grp >= P.n_groups) return;
-    const int64_t o =
-        P.row_obj ? (int64_t)P.row_obj[grp * P.rows_per_group] : grp;  // uniform per group
-    // (without row_obj, row r belongs to object r / rows_per_group, so group g is object g)
-    if (o < 0 || o >= P.n_obj) return;
+    const int64_t o = group_object(P, grp);  // uniform per group
+    if (o < 0) return;
     const ObjMeta m = P.meta[o];
     PeakRec best{0.0, -1};
     if (m.status == LSP_OBJ_OK) {
@@ -66,12 +44,7 @@ __global__ __launch_bounds__(kPeakThreads) void peaks_kernel(const PeakParams P)
 // The FP32 forms' groups: one thread per group decodes the group's peak key.
 __global__ __launch_bounds__(kPeakThreads) void peaks_from_keys_kernel(const PeakParams P) {
     const int64_t grp = linear_block() * kPeakThreads + threadIdx.x;
-    if (grp >= P.n_groups) return;
-    const int64_t o = P.row_obj ? (int64_t)P.row_obj[grp * P.rows_per_group] : grp;
-    if (o < 0 || o >= P.n_obj) return;
-    const ObjMeta m = P.meta[o];
-    const PeakRec b = m.status == LSP_OBJ_OK ? key_peak(P.keys[grp]) : PeakRec{0.0, -1};
-    P.peaks[o] = make_peak(P, m, b);
+    if (grp < P.n_groups) write_key_peak(P, grp);
 }
 
 __global__ void fill_u32_kernel(unsigned int* dst, int64_t n, unsigned int v) {
