@@ -231,7 +231,7 @@ static_assert(kFxBins == kFxTile, "one record per wave tile");
 
 // The fix-up writes the peaks itself where its last workgroup has a thread for
 // each group and there are few workgroups to wait for.  With the clearing done
-// by the statistics kernel, a series of 150 points on 5,000 bins takes 19 us, 26
+// by the statistics kernel, a series of 256 points on 10,000 bins takes 19 us, 26
 // us with kernels of their own for both.  (The FP64 form's last workgroup was no faster
 // than a kernel, 23.9 against 24.1 us: it has records to read.)
 constexpr int64_t kMaxLastWg = 256;
