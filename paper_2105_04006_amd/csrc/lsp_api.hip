@@ -316,7 +316,7 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     // tiles of 500 points 85 / 60; 2,000 tiles of 300 points 99 / 111.  The
     // count is that of the whole batch, so that parts of it (row mode, the
     // host-return chunks) add their sums in the same order.
-    const int64_t wave_bins = !f32 ? kFxTile : method.gen ? kMxTile : 2 * kMxTile;
+    const int64_t wave_bins = f32 ? mx_item_bins(1, false, method.gen) : kFxTile;
     const int64_t count = rows.n_batch * rows.rows_per_group * ((n_f + wave_bins - 1) / wave_bins);
     const bool split = count <= (f32 && rows.n_batch > 1 ? 400 : 1024);
     int waves;
@@ -327,7 +327,7 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     else
         waves = method.gen || n_f > 2 * wave_bins ? 4 : (n_f > wave_bins ? 2 : 1);
     const int64_t bins = f32 ? mx_item_bins(waves, split, method.gen) : fx_item_bins(waves, split);
-    const int64_t tile = f32 ? kMxTile : kFxTile;
+    const int64_t tile = !f32 ? kFxTile : method.gen ? kMxTileGen : kMxTile;
     const int64_t tiles = (n_f + tile - 1) / tile;
     if (tiles * rows.rows_per_group > kMaxGrid / rows.n_rows) return LSP_OK;
     c->mx = split ? kMxSplit : kMxTiles;

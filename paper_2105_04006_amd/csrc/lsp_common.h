@@ -46,9 +46,10 @@ struct ObjMeta {
 };
 static_assert(sizeof(ObjMeta) == 64, "ObjMeta layout");
 
-// Bins of a fix-up tile of the FP32 matrix-core kernels (lsp_mx.hip), and of a
-// peak record of the FP64 ones (lsp_fx.hip).
+// Bins of a fix-up tile of the FP32 matrix-core kernels (lsp_mx.hip), standard
+// and generalized, and of a peak record of the FP64 ones (lsp_fx.hip).
 constexpr int kMxTile = 1024;
+constexpr int kMxTileGen = 512;
 constexpr int kFxTile = 512;
 
 // The matrix-core kernels scale an object's centred magnitudes by 2^e with

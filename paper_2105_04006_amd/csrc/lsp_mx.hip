@@ -118,14 +118,15 @@ __device__ __forceinline__ unsigned long long finish_wave(const MainParams& P, c
                                                           const f16v (&acc)[8], int64_t row,
                                                           int64_t w0, int64_t f_lo, int lane) {
     const int sub = lane & 31, half = lane >> 5;
+    constexpr int kRowsFix = 16 * kFix / kWaveBins;  // accumulator rows of a fix-up tile
     float p[16][2];
-    unsigned long long best = 0ull;
+    LaneBest lb;
 #pragma unroll
     for (int t = 0; t < kWaveBins / kFix; ++t) {
-        LaneBest lb;
+        LaneBest lt;
         bool ill = false;
 #pragma unroll
-        for (int r = 8 * t; r < 8 * t + 8; ++r) {
+        for (int r = kRowsFix * t; r < kRowsFix * (t + 1); ++r) {
             float v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = acc[q][r];
@@ -136,18 +137,19 @@ __device__ __forceinline__ unsigned long long finish_wave(const MainParams& P, c
                 const int a = 8 * (r / 4) + 4 * half + (r & 3);
                 const bool in = WHOLE || tile_bin(a, sub, e) < R.left;
                 ill |= bad[e] & in;
-                lb.offer(in ? p[r][e] : -1.0f, 2 * r + e);
+                lt.offer(in ? p[r][e] : -1.0f, 2 * r + e);
             }
         }
-        if (__any(ill)) {
+        if (__any(ill)) {  // the fix-up's: it offers the tile's bins itself
             const int64_t tile = row * P.tiles_per_row + (w0 - f_lo) / kFix + t;
             if (lane == 0) atomicOr(&P.ill_bits[tile >> 5], 1u << (tile & 31));
         } else {
-            const int r = lb.bin >> 1;
-            lb.bin = tile_bin(8 * (r >> 2) + 4 * half + (r & 3), sub, lb.bin & 1);
-            best = umax64(best, wave_key(lb, w0));
+            lb.offer(lt.p, lt.bin);
         }
     }
+    const int r = lb.bin >> 1;
+    lb.bin = tile_bin(8 * (r >> 2) + 4 * half + (r & 3), sub, lb.bin & 1);
+    const unsigned long long best = wave_key(lb, w0);
     if (R.pgram)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -345,12 +347,13 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        // rows 0..7 of the accumulators (waves 0..3) are the first fix-up tile
+        // eight rows of the accumulators (four waves) are a fix-up tile
+        constexpr int kPer = kSplitW * kFix / kWaveBins;
         unsigned long long best = 0ull;
         for (int t = 0; t < kWaveBins / kFix; ++t) {
             int bad = 0;
             unsigned long long k = 0ull;
-            for (int w = 4 * t; w < 4 * t + 4; ++w) {
+            for (int w = kPer * t; w < kPer * (t + 1); ++w) {
                 bad |= s_ill[w];
                 k = umax64(k, s_key[w]);
             }
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
 //   w c, w s, w yw c, w yw s, w (cos 2)/2, w (sin 2)/2
 // against the same four offset factors.  Twelve accumulators of a 32 x 32 tile
 // would leave one wave per SIMD, so a wave's tile is 16 blocks x 32 offsets
-// (1,024 bins, one fix-up tile) on v_mfma_f32_16x16x32_f16: 72 matrix
+// (1,024 bins, two fix-up tiles) on v_mfma_f32_16x16x32_f16: 72 matrix
 // instructions per 32 observations.  Measured, vector kernels -> here: 4,096
 // points with errors on 500,000 bins 422 -> 124 us; error 1.1e-6 -> 2.3e-7.
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -380,7 +383,8 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 constexpr int kGSlice = 32;                  // observations per matrix instruction
 constexpr int kGRows = 16;                   // blocks per wave tile
 constexpr int kGBins = kBlk * kGRows;        // 1,024 bins
-static_assert(kGBins == kFix, "a generalized wave tile is one fix-up tile");
+constexpr int kFixG = kMxTileGen;            // bins per fix-up tile
+static_assert(kGBins == 2 * kFixG, "a generalized wave tile is two fix-up tiles");
 
 // Centre factors of 8 observations: q[0..5] hi, q[6..11] lo halves.
 struct FragG {
@@ -494,6 +498,21 @@ __device__ __forceinline__ void stage_g(const MainParams& P, const ObjMeta& m, i
     }
 }
 
+// The first fix-up tile of a wave's 1,024 bins is in lanes 0..31 (blocks 0..7),
+// the second in the others: bit h of the result is set where half h has an
+// ill-conditioned bin.
+__device__ __forceinline__ uint32_t ill_halves(bool ill) {
+    const unsigned long long m = __ballot(ill);
+    return ((uint32_t)m ? 1u : 0u) | ((uint32_t)(m >> 32) ? 2u : 0u);
+}
+
+// Leaves fix-up tiles `tile` and `tile` + 1 to the fix-up, by bit.
+__device__ __forceinline__ void mark_ill(const MainParams& P, int64_t tile, uint32_t bad,
+                                         int lane) {
+    if (lane < 2 && ((bad >> lane) & 1u))
+        atomicOr(&P.ill_bits[(tile + lane) >> 5], 1u << ((tile + lane) & 31));
+}
+
 // Finish one wave's 1,024 bins from complete sums acc[offset half][12].
 template <bool WHOLE>
 __device__ __forceinline__ void finish_tile_g(const MainParams& P, const FinishG& R, int64_t row,
@@ -523,14 +542,12 @@ __device__ __forceinline__ void finish_tile_g(const MainParams& P, const FinishG
             lb.offer(in ? p[r][e] : -1.0f, 4 * r + e);
         }
     }
-    if (__any(ill)) {
-        const int64_t bit = row * P.tiles_per_row + tile;
-        if (lane == 0) atomicOr(&P.ill_bits[bit >> 5], 1u << (bit & 31));
-    } else {
-        lb.bin = bin_of(lb.bin >> 2, lb.bin & 3);
-        const unsigned long long best = wave_key(lb, w0);
-        if (lane == 0 && best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
-    }
+    lb.bin = bin_of(lb.bin >> 2, lb.bin & 3);
+    const uint32_t bad = ill_halves(ill);
+    mark_ill(P, row * P.tiles_per_row + tile, bad, lane);
+    if ((bad >> (lane >> 5)) & 1u) lb.p = -1.0f;
+    const unsigned long long best = wave_key(lb, w0);
+    if (lane == 0 && best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
     if (R.out.pgram)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -612,7 +629,7 @@ __global__ __launch_bounds__(kWave* kGW, 2) void mx_gen_tile_kernel(const MainPa
     }
     const FinishG R = make_finish_g(P, m, rr, w0);
     if (R.out.left <= 0) return;
-    const int64_t tile = (w0 - rr.f_lo) / kFix;
+    const int64_t tile = (w0 - rr.f_lo) / kFixG;
     if (R.out.left == kGBins)
         finish_tile_g<true>(P, R, row, tile, w0, acc, lane);
     else
@@ -629,7 +646,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
     __shared__ float s_w[kGSplitObs], s_wy[kGSplitObs];
     __shared__ float s_sum[2][kSplitW][8][kWave];  // 8 = offset halves x accumulator rows
     __shared__ unsigned long long s_key[kSplitW];
-    __shared__ int s_ill[kSplitW];
+    __shared__ uint32_t s_ill[kSplitW];
 
     const int64_t b = linear_block();
     if (b >= P.n_items) return;
@@ -705,26 +722,22 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
         lb.offer(in ? p : -1.0f, bin);
         if (R.out.pgram) R.out.store(w0, bin, p);
     }
-    const unsigned long long key = wave_key(lb, w0);
-    const bool any = __any(ill);
-    if (lane == 0) {
-        s_key[wave] = key;
-        s_ill[wave] = any;
-    }
+    const uint32_t any = ill_halves(ill);
+    if (lane == 0) s_ill[wave] = any;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int bad = 0;
+    uint32_t bad = 0u;
+#pragma unroll
+    for (int w = 0; w < kSplitW; ++w) bad |= s_ill[w];
+    if ((bad >> (lane >> 5)) & 1u) lb.p = -1.0f;
+    const unsigned long long key = wave_key(lb, w0);
+    if (lane == 0) s_key[wave] = key;
+    __syncthreads();
+    if (wave != 0) return;
+    mark_ill(P, row * P.tiles_per_row + (w0 - rr.f_lo) / kFixG, bad, lane);
+    if (lane == 0) {
         unsigned long long best = 0ull;
-        for (int w = 0; w < kSplitW; ++w) {
-            bad |= s_ill[w];
-            best = umax64(best, s_key[w]);
-        }
-        if (bad) {
-            const int64_t tile = row * P.tiles_per_row + (w0 - rr.f_lo) / kFix;
-            atomicOr(&P.ill_bits[tile >> 5], 1u << (tile & 31));
-        } else if (best != 0ull) {
-            atomicMax(&P.keys[row / P.rows_per_group], best);
-        }
+        for (int w = 0; w < kSplitW; ++w) best = umax64(best, s_key[w]);
+        if (best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
     }
 }
 
