@@ -16,7 +16,7 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
 
     const int64_t b = linear_block();
     if (b >= P.n_items) return;
-    const int64_t item = xcd_remap(b, P.n_items);
+    const int64_t item = mx_item(P.row_perm, P.row_obj, b, P.n_items);
     const int64_t rank = item / P.chunks_per_row;
     const int64_t chunk = item - rank * P.chunks_per_row;
     const int64_t row = item_row(P.row_perm, rank);
