@@ -48,6 +48,12 @@ FLOPS_PER_EVAL_GEN = 16
 # MI355X FP32 vector peak: 256 CUs x 4 SIMDs x 2.4 GHz x 64 flops/clock/SIMD
 # (32 FMA lanes per clock), the published 157.3 TFLOP/s.
 PEAK_FP32_TFLOPS = 256 * 4 * 2.4e9 * 64 / 1e12
+# Matrix-core form (what runs when every tuning option is left to the library):
+# 4 multiply-adds per evaluation (6 generalized), each as three products of
+# 11-bit halves on the FP16 matrix instructions, against their dense peak
+# (1,024 flops per clock and SIMD).
+FLOPS_PER_EVAL_MATRIX = {"standard": 24, "generalized": 36}
+PEAK_FP16_MATRIX_TFLOPS = 256 * 4 * 2.4e9 * 1024 / 1e12
 # VALU instructions per observation and lane in the compiled gfx950 loop, for
 # K frequencies per lane: 4K for the sums, the recurrence (4(K-1) for rotations;
 # 4 + 2(K-2) for Chebyshev), and 9-10 per-observation instructions (FP64
@@ -64,7 +70,44 @@ def valu_ops_per_eval_gen(k):
     return (6 * k + 4 + 2 * (k - 2) + 12) / k
 
 
-# the kernel's sources and the file that resolves its launch shape (waves,
+def roofline(args, gen, rec_name, k_lane, evals, k_ms, workload, variant=False):
+    """The dominant kernel's rate against the peak of the units that it uses."""
+    matrix = not (variant or args.k or args.waves or args.t_split) and \
+        args.recurrence == args.wave_split == args.schedule == "auto"
+    if matrix:
+        flops_eval = FLOPS_PER_EVAL_MATRIX["generalized" if gen else "standard"]
+        peak, valu = PEAK_FP16_MATRIX_TFLOPS, None
+    else:
+        flops_eval = FLOPS_PER_EVAL_GEN if gen else FLOPS_PER_EVAL[rec_name]
+        peak = PEAK_FP32_TFLOPS
+        valu = (valu_ops_per_eval_gen(k_lane) if gen else valu_ops_per_eval(rec_name, k_lane)) \
+            * evals / (k_ms * 1e-3)
+    vector = None if variant else valu
+    achieved = flops_eval * evals / (k_ms * 1e-3) / 1e12
+    return {
+        "bound": "alu",
+        "achieved": achieved,
+        "peak": peak,
+        "unit": "TFLOP/s",
+        "frac": achieved / peak,
+        "traffic": None if variant or matrix else measured_traffic(args.method, workload),
+        "kernel": ("mx_gen_kernel" if gen else "mx_kernel") if matrix
+        else "gen_fp32p_kernel" if gen else "fp32p_kernel",
+        "kernel_ms": k_ms,
+        "flops_per_eval": flops_eval,
+        "evals_per_launch": int(evals),
+        "matrix_cores": matrix,
+        "recurrence": None if matrix else rec_name,
+        "k_per_lane": None if matrix else k_lane,
+        "valu_lane_ops_per_s": vector,
+        "valu_issue_frac": None if vector is None else vector / (PEAK_FP32_TFLOPS * 1e12 / 2),
+        "obs_read": args.obs_read,
+        "seed_trig": args.seed_trig,
+        "transcendentals_per_s": None if matrix else 2 * evals / k_lane / (k_ms * 1e-3),
+    }
+
+
+# the vector kernel's sources and the file that resolves its launch shape (waves,
 # splits, items), on which the counters depend as much
 KERNEL_SOURCES = {
     "standard": ["paper_2105_04006_amd/csrc/lsp_fp32p.hip", "paper_2105_04006_amd/csrc/lsp_common.h",
@@ -341,10 +384,6 @@ def main():
     rec_name = "rotation" if p32.launch()["recurrence"] == lsp.REC_ROTATION else "chebyshev"
     shape = p32.launch()
     k_lane = shape["k_per_lane"]
-    flops_eval = FLOPS_PER_EVAL_GEN if gen else FLOPS_PER_EVAL[rec_name]
-    achieved = flops_eval * evals / (k_ms * 1e-3) / 1e12
-    valu_ops = (valu_ops_per_eval_gen(k_lane) if gen else valu_ops_per_eval(rec_name, k_lane)) \
-        * evals / (k_ms * 1e-3)
     out = {
         "metric": METRIC,
         "value": value,
@@ -373,24 +412,7 @@ def main():
         "peak_bin_agreement": float(agree.mean()),
         "generalized_vs_standard": std_cost,
         "max_abs_dpower_vs_fp64": d,
-        "roofline": {
-            "bound": "alu",
-            "achieved": achieved,
-            "peak": PEAK_FP32_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": achieved / PEAK_FP32_TFLOPS,
-            "traffic": None if variant else measured_traffic(args.method, w.name),
-            "kernel": "gen_fp32p_kernel" if gen else "fp32p_kernel",
-            "kernel_ms": k_ms,
-            "flops_per_eval": flops_eval,
-            "recurrence": rec_name,
-            "k_per_lane": k_lane,
-            "valu_lane_ops_per_s": None if variant else valu_ops,
-            "valu_issue_frac": None if variant else valu_ops / (PEAK_FP32_TFLOPS * 1e12 / 2),
-            "obs_read": args.obs_read,
-            "seed_trig": args.seed_trig,
-            "transcendentals_per_s": 2 * evals / k_lane / (k_ms * 1e-3),
-        },
+        "roofline": roofline(args, gen, rec_name, k_lane, evals, k_ms, w.name, variant),
         "cpu_baseline": None,
     }
     if not args.no_cpu:
@@ -894,10 +916,6 @@ def bench_forms(args, torch, dev):
 
     rec_name = "rotation" if shape["recurrence"] == lsp.REC_ROTATION else "chebyshev"
     k_lane = shape["k_per_lane"]
-    flops_eval = FLOPS_PER_EVAL_GEN if gen else FLOPS_PER_EVAL[rec_name]
-    achieved = flops_eval * w.evals / (k_ms * 1e-3) / 1e12
-    valu_ops = (valu_ops_per_eval_gen(k_lane) if gen else valu_ops_per_eval(rec_name, k_lane)) \
-        * w.evals / (k_ms * 1e-3)
     out = {
         "metric": METRIC,
         "value": w.evals / (ms32 * 1e-3),
@@ -920,23 +938,7 @@ def bench_forms(args, torch, dev):
                    "output": "peaks", "method": method},
         "objects_per_s": w.n_obj / (ms32 * 1e-3),
         "forms": form_rec,
-        "roofline": {
-            "bound": "alu",
-            "achieved": achieved,
-            "peak": PEAK_FP32_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": achieved / PEAK_FP32_TFLOPS,
-            "traffic": measured_traffic(args.method, w.name),
-            "kernel": "gen_fp32p_kernel" if gen else "fp32p_kernel",
-            "kernel_ms": k_ms,
-            "flops_per_eval": flops_eval,
-            "evals_per_launch": int(w.evals),
-            "recurrence": rec_name,
-            "k_per_lane": k_lane,
-            "valu_lane_ops_per_s": valu_ops,
-            "valu_issue_frac": valu_ops / (PEAK_FP32_TFLOPS * 1e12 / 2),
-            "transcendentals_per_s": 2 * w.evals / k_lane / (k_ms * 1e-3),
-        },
+        "roofline": roofline(args, gen, rec_name, k_lane, w.evals, k_ms, w.name),
         "cpu_baseline": None,
     }
     if not args.no_cpu:
