@@ -40,6 +40,7 @@ namespace lsp {
 typedef double fx_d4 __attribute__((ext_vector_type(4)));
 typedef float fx_f4 __attribute__((ext_vector_type(4)));
 typedef float fx_f2 __attribute__((ext_vector_type(2)));
+typedef double fx_d2 __attribute__((ext_vector_type(2)));
 typedef _Float16 fx_h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 fx_h8 __attribute__((ext_vector_type(8)));
 
@@ -162,21 +163,71 @@ __device__ __forceinline__ void fx_sincos(double f, double hi, double lo, double
     *cs = __longlong_as_double(__double_as_longlong(cx) ^ (((q + 1) & 2) ? top : 0ull));
 }
 
+// Offset factors of one round of steps, in two buffers, for the waves of a
+// workgroup that have tiles of one row: the FP64 cosine and sine, and the four
+// f16 factors.
+struct FxOffsets {
+    fx_d2 x[2][kFxSteps][kWave];
+    fx_h8 h[2][4][kWave];
+};
+
+struct FxOffset {
+    double c, s;
+    _Float16 h[4];
+};
+
+__device__ __forceinline__ FxOffset fx_make_offset(double H, double th, double tl) {
+    FxOffset o;
+    fx_sincos(H, th, tl, &o.s, &o.c);
+    const float cf = (float)o.c, sf = (float)o.s;
+    const fx_h2 b1 = __builtin_convertvector((fx_f2){cf, sf}, fx_h2);
+    o.h[0] = b1.x;
+    o.h[1] = b1.y;
+    o.h[2] = (_Float16)fmaf(cf, cf, -0.5f);
+    o.h[3] = (_Float16)(cf * sf);
+    return o;
+}
+
 // Add the steps [lo, hi) of four staged observations each to the wave's sums.
 // Lane (row or column lane % 16, quarter lane / 16) supplies observation
 // 4 step + quarter to both operands; eight steps feed one f16 product.
-template <bool GEN>
+// WAVES > 0: all WAVES waves of the workgroup call with the same steps and H,
+// make the offset factors of 8 / WAVES steps each and share them through O
+// (48 objects of 50 to 1,000 points on 40,000 bins: 379 -> 357 us).
+template <bool GEN, int WAVES = 0>
 __device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>& S, int cnt,
-                                              int lo, int hi, double G, double H, int lane) {
+                                              int lo, int hi, double G, double H, int lane,
+                                              FxOffsets* O = nullptr, int wave = 0) {
     constexpr int NG = FxSums<GEN>::kSums;
     const int quarter = lane >> 4;
     for (int s0 = lo; s0 < hi; s0 += kFxSteps) {
         const int steps = hi - s0 < kFxSteps ? hi - s0 : kFxSteps;
         fx_h8 ah[2 * NG], bh[4];
+        const int buf = ((s0 - lo) / kFxSteps) & 1;
+        if constexpr (WAVES > 0) {
+            constexpr int kMine = kFxSteps / WAVES;
+            _Float16 mine[4][kMine];
+#pragma unroll
+            for (int e = 0; e < kMine; ++e) {
+                const int s = wave * kMine + e;
+                const int j = 4 * (s < steps ? s0 + s : s0) + quarter;  // (past the end: unused)
+                const FxOffset o = fx_make_offset(H, S.hi[j], S.lo[j]);
+                O->x[buf][s][lane] = fx_d2{o.c, o.s};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) mine[q][e] = o.h[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < kMine; ++e)
+                    reinterpret_cast<_Float16*>(&O->h[buf][q][lane])[wave * kMine + e] = mine[q][e];
+            __syncthreads();
+        }
 #pragma unroll
         for (int q = 0; q < 2 * NG; ++q) ah[q] = fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bh[q] = fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int q = 0; q < 4; ++q)
+            bh[q] = WAVES > 0 ? O->h[buf][q][lane] : fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < kFxSteps; ++s) {
             if (s < steps) {
@@ -206,14 +257,18 @@ __device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>
                 ah[2 * NG - 2][s] = (_Float16)(wt * fmaf(cf, cf, -0.5f));
                 ah[2 * NG - 1][s] = (_Float16)(wt * (cf * sf));
                 double bs, bc;
-                fx_sincos(H, th, tl, &bs, &bc);
+                if constexpr (WAVES > 0) {
+                    const fx_d2 b = O->x[buf][s][lane];
+                    bc = b[0];
+                    bs = b[1];
+                } else {
+                    const FxOffset o = fx_make_offset(H, th, tl);
+                    bc = o.c;
+                    bs = o.s;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bh[q][s] = o.h[q];
+                }
                 const double b2c = fma(bc, bc, -0.5), b2s = bc * bs;
-                const float bcf = (float)bc, bsf = (float)bs;
-                const fx_h2 b1 = __builtin_convertvector((fx_f2){bcf, bsf}, fx_h2);
-                bh[0][s] = b1.x;
-                bh[1][s] = b1.y;
-                bh[2][s] = (_Float16)fmaf(bcf, bcf, -0.5f);
-                bh[3][s] = (_Float16)(bcf * bsf);
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
                     const double c = g + 1 == NG ? b2c : bc, z = g + 1 == NG ? b2s : bs;

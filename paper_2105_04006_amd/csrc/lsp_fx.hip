@@ -3,6 +3,8 @@
 #include "lsp_fx.h"
 #include "lsp_peaks.h"
 
+#include <type_traits>
+
 namespace lsp {
 namespace {
 
@@ -11,7 +13,8 @@ namespace {
 template <bool GEN, int W, bool SPLIT>
 __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
     __shared__ FxStage<GEN> S;
-    __shared__ double s_buf[SPLIT ? W : 1][8][kWave];
+    // the split's partial sums, or the shared offset factors
+    __shared__ typename std::conditional<SPLIT, double[W][8][kWave], FxOffsets>::type s_buf;
     __shared__ PeakRec s_red[W];
 
     const int64_t b = linear_block();
@@ -71,7 +74,10 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
             __syncthreads();
             int lo, hi;
             fx_share<SPLIT ? W : 1>(cnt, SPLIT ? uniform_i32(wave) : 0, &lo, &hi);
-            fx_accumulate(A, S, cnt, lo, hi, G, H, lane);
+            if constexpr (SPLIT)
+                fx_accumulate(A, S, cnt, lo, hi, G, H, lane);
+            else
+                fx_accumulate<GEN, W>(A, S, cnt, lo, hi, G, H, lane, &s_buf, uniform_i32(wave));
         }
         constexpr int NQ = 4 * FxSums<GEN>::kSums;
         double xs[SPLIT ? NQ : 1];
