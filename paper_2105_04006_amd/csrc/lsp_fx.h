@@ -88,13 +88,22 @@ __device__ __forceinline__ FxScales fx_scales(const ObjMeta& m) {
     return s;
 }
 
+// Steps of a wave with a tile of its own that are taken together, without a
+// branch between them, so that their chains of dependent FP64 operations
+// overlap; a pass is padded to whole groups with observations that weigh nothing.
+// Steps alone, in twos, in fours: 48 objects of 50 to 1,000 points on 40,000 bins
+// 357, 301 and 312 us (kernel); 1,000 generalized ones on 50,000 bins 4.47, 3.90
+// and 3.79 ms.
+constexpr int fx_group(bool gen) { return gen ? 4 : 2; }
+
 template <bool GEN>
 __device__ __forceinline__ void fx_stage(FxStage<GEN>& S, const ObjMeta& m,
                                          const double* __restrict__ t,
                                          const double* __restrict__ y,
                                          const double* __restrict__ dy, int64_t jt, int cnt,
                                          const FxScales& sc, int threads) {
-    const int padded = (cnt + 3) / 4 * 4;
+    constexpr int kGroup = 4 * fx_group(GEN);
+    const int padded = (cnt + kGroup - 1) / kGroup * kGroup;
     for (int q = threadIdx.x; q < padded; q += threads) {
         const int64_t j = m.j0 + jt + q;
         double hi = 0.0, lo = 0.0, u = 0.0, w = 0.0;
@@ -228,9 +237,12 @@ __device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             bh[q] = WAVES > 0 ? O->h[buf][q][lane] : fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
+        constexpr int kGroup = WAVES > 0 ? fx_group(GEN) : 1;
 #pragma unroll
-        for (int s = 0; s < kFxSteps; ++s) {
-            if (s < steps) {
+        for (int sg = 0; sg < kFxSteps; sg += kGroup) {
+            if (sg >= steps) break;
+#pragma unroll
+            for (int s = sg; s < sg + kGroup; ++s) {
                 const int j = 4 * (s0 + s) + quarter;
                 const double th = S.hi[j], tl = S.lo[j], u = S.u[j];
                 const double one = j < cnt ? 1.0 : 0.0;  // padding weighs nothing

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
         FxSums<GEN> A;
         fx_zero(A);
         for (int64_t jt = 0; jt < m.n; jt += kFxObs) {
-            const int cnt = (int)(m.n - jt < kFxObs ? m.n - jt : kFxObs);
+            const int cnt = uniform_i32((int)(m.n - jt < kFxObs ? m.n - jt : kFxObs));
             __syncthreads();
             fx_stage(S, m, P.t, P.y, P.dy, jt, cnt, sc, kWave * W);
             __syncthreads();
