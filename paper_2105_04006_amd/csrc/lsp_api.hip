@@ -313,15 +313,16 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     // 500 points 45 / 26, of 100 points 24 / 21; 500 tiles 48 / 40 and (60
     // points) 22 / 26; 1,000 tiles of 200 points 39 / 49, of 1,000 points
     // 108 / 93; one series of 4,096 points, 1,954 tiles, 463 / 575.  FP64: 400
-    // tiles of 500 points 85 / 60; 2,000 tiles of 300 points 99 / 111.  The
+    // tiles of 500 points 77 / 61, of 60 points 26 / 31; 782 tiles of one series
+    // of 2,000 points 251 / 267; 800 tiles of 300 points 55 / 62.  The
     // count is that of the whole batch, so that parts of it (row mode, the
     // host-return chunks) add their sums in the same order.
     const int64_t wave_bins = f32 ? mx_item_bins(1, false, method.gen) : kFxTile;
     const int64_t count = rows.n_batch * rows.rows_per_group * ((n_f + wave_bins - 1) / wave_bins);
-    const bool split = count <= (f32 && rows.n_batch > 1 ? 400 : 1024);
+    const bool split = count <= (!f32 ? 512 : rows.n_batch > 1 ? 400 : 1024);
     int waves;
     if (!f32)
-        waves = split && count <= 512 ? 8 : 4;
+        waves = split ? 8 : 4;
     else if (split)
         waves = 8;
     else

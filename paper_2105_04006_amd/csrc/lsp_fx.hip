@@ -263,9 +263,7 @@ static hipError_t launch_fx_g(const MainParams& p, int waves, bool split, hipStr
     const dim3 grid = grid_for(p.n_items);
     if (split && waves == 8)
         hipLaunchKernelGGL((fx_kernel<GEN, 8, true>), grid, dim3(kWave * 8), 0, s, p);
-    else if (split && waves == 4)
-        hipLaunchKernelGGL((fx_kernel<GEN, 4, true>), grid, dim3(kWave * 4), 0, s, p);
-    else if (waves == 4)
+    else if (!split && waves == 4)
         hipLaunchKernelGGL((fx_kernel<GEN, 4, false>), grid, dim3(kWave * 4), 0, s, p);
     else
         return hipErrorInvalidValue;
