@@ -22,10 +22,10 @@
 // cycles at their rate of 16 multiply-adds a cycle) and about 70 FP64 vector
 // instructions for its factors, which the FP64 units execute in turn: the two
 // bound it together.  Measured, a sine and cosine per (bin, observation) ->
-// here: 48 objects of 50..1,000 points on 40,000 bins 1984 -> 388 us; 256
+// here: 48 objects of 50..1,000 points on 40,000 bins 2,250 -> 330 us; 256
 // points on 10,000 bins 82 -> 24 us; 100 objects of 520 points on 40,000 bins
 // 3.9e12 (observation, bin) pairs a second; the FP64 recompute of 300
-// asteroid-like objects 1370 -> 160 us.  The error against an extended-
+// asteroid-like objects 1370 -> 78 us.  The error against an extended-
 // precision evaluation is unchanged (3.8e-15 of the 2-norm).
 //
 // A bin whose smaller denominator (N - R, or T - R) is at most N/256 loses more
