@@ -60,16 +60,18 @@ constexpr int kRowsA = 32;                    // blocks per wave tile
 constexpr int kWaveBins = kBlk * kRowsA;      // 2,048 bins
 constexpr int kFix = kMxTile;                 // bins per fix-up tile
 
-// hi and lo halves of two values: hi = f16(x), lo = f16(x - hi).
+// hi and lo halves of two values: hi = f16(x), lo = f16(x - hi); x - hi is exact.
+// Two mixed-precision fused multiply-adds (where the compiler does not know
+// that their factor is -1) and a conversion of the pair.  Never as inline
+// assembly: the compiler does not see what such an instruction writes, and in a
+// generalized kernel it left one of the two wait states that the matrix
+// instruction after it needs.  (v_fma_mixlo_f16 and v_fma_mixhi_f16, written
+// so, were also slower: a survey batch 4,285 -> 4,194 us.)
 __device__ __forceinline__ void split2(float x, float y, h2& hi, h2& lo) {
     hi = __builtin_convertvector((f2){x, y}, h2);
-    const float m1 = -1.0f;
-    // f16(x - hi) in one instruction each (a mixed-precision fused multiply-add
-    // into the low, then the high half; x - hi is exact, so it rounds once)
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(m1), "v"(x));
-    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
-        : "+v"(lo)
-        : "v"(hi), "v"(m1), "v"(y));
+    float m1 = -1.0f;
+    asm("" : "+s"(m1));
+    lo = h2{(_Float16)fmaf((float)hi.x, m1, x), (_Float16)fmaf((float)hi.y, m1, y)};
 }
 
 __device__ __forceinline__ void put2(h8& v, int p, h2 x) {
