@@ -15,8 +15,8 @@
 // and since e is that small D needs few digits: it is accumulated from f16
 // factors on v_mfma_f32_16x16x32_f16.  Where 2 pi e tau could exceed 1e-9
 // (kFxResidual), so that D's rounding or the second order could show, the bins
-// are evaluated one by one instead (power64_bin), as are those of objects of up
-// to four points, whose moment matrix is often close to singular.
+// are evaluated one by one instead (fx_direct), as are those of objects of a
+// few points (fx_few), whose moment matrix is often close to singular.
 //
 // Per four observations a 512-bin tile takes eight matrix instructions (512
 // cycles at their rate of 16 multiply-adds a cycle) and about 70 FP64 vector
@@ -29,8 +29,9 @@
 // precision evaluation is unchanged (3.8e-15 of the 2-norm).
 //
 // A bin whose smaller denominator (N - R, or T - R) is at most N/256 loses more
-// than two digits of it to cancellation; its sums are taken again term by term
-// (fx_bin_wave), the observations shared out over the wavefront.
+// than two digits of it to cancellation; it goes to a list of the workgroup's,
+// and its sums are taken again term by term when the matrix sums are done
+// (fx_direct).
 #pragma once
 
 #include "lsp_common.h"
@@ -51,7 +52,14 @@ constexpr int kFxSteps = 8;             // FP64 matrix steps (four observations)
 constexpr int kFxObs = 256;             // observations staged per pass
 constexpr double kFxResidual = 1e-9;
 constexpr double kFxIll = 1.0 / 256.0;
-constexpr int kFxFew = 4;               // objects of up to this many points: bin by bin
+// Objects of up to this many points are evaluated bin by bin, in a tile of their
+// own and in the fix-up, whose waves share one.  Measured, bin by bin / matrix
+// (us): 2,000 objects on 10,000 bins, 4 points 317 / 428, 5 points 346 / 266, with
+// errors 6 points 330 / 354, 8 points 391 / 292; fix-up of 300 objects of two to four
+// clumps on 20,000 bins, 16 points 970 / 1,106, 24 points 1,270 / 1,211, with errors
+// 32 points 783 / 905, 48 points 1,016 / 948.
+constexpr int fx_few(bool gen) { return gen ? 6 : 4; }
+constexpr int fx_few_fix(bool gen) { return gen ? 32 : 20; }
 
 // Sums of a wave tile.  Complex sums: the standard form has sum y e and
 // sum e^2 / 2, the generalized one sum w e, sum w yw e and sum w e^2 / 2
@@ -202,11 +210,13 @@ __device__ __forceinline__ FxOffset fx_make_offset(double H, double th, double t
 // 4 step + quarter to both operands; eight steps feed one f16 product.
 // WAVES > 0: all WAVES waves of the workgroup call with the same steps and H,
 // make the offset factors of 8 / WAVES steps each and share them through O
-// (48 objects of 50 to 1,000 points on 40,000 bins: 379 -> 357 us).
+// (48 objects of 50 to 1,000 points on 40,000 bins: 379 -> 357 us).  A wave
+// without a tile (idle) makes its share only.
 template <bool GEN, int WAVES = 0>
 __device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>& S, int cnt,
                                               int lo, int hi, double G, double H, int lane,
-                                              FxOffsets* O = nullptr, int wave = 0) {
+                                              FxOffsets* O = nullptr, int wave = 0,
+                                              bool idle = false) {
     constexpr int NG = FxSums<GEN>::kSums;
     const int quarter = lane >> 4;
     for (int s0 = lo; s0 < hi; s0 += kFxSteps) {
@@ -231,6 +241,7 @@ __device__ __forceinline__ void fx_accumulate(FxSums<GEN>& A, const FxStage<GEN>
                 for (int e = 0; e < kMine; ++e)
                     reinterpret_cast<_Float16*>(&O->h[buf][q][lane])[wave * kMine + e] = mine[q][e];
             __syncthreads();
+            if (idle) continue;
         }
 #pragma unroll
         for (int q = 0; q < 2 * NG; ++q) ah[q] = fx_h8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -323,53 +334,14 @@ __device__ __forceinline__ void fx_zero(FxSums<GEN>& A) {
     }
 }
 
-__device__ __forceinline__ double fx_wave_sum(double v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
-// Power at frequency f (cycles; the same in every lane) from sums taken term by
-// term, the observations shared out over the wavefront.  Called by all lanes.
-template <bool GEN>
-__device__ __noinline__ double fx_bin_wave(const ObjMeta& m, const double* __restrict__ t,
-                                           const double* __restrict__ y,
-                                           const double* __restrict__ dy, double f, int lane) {
-    double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t j = m.j0 + lane; j < m.j0 + m.n; j += kWave) {
-        double s, c, hi, lo;
-        recentre64(t[j], m.t0, &hi, &lo);
-        sincos_cycles64(f, hi, lo, &s, &c);
-        const double w = GEN ? gen_weight(dy, j, m.wnorm) : 1.0;
-        const double u = w * (y[j] - m.ybar);
-        if (GEN) {
-            v[5] += w * c;
-            v[6] += w * s;
-        }
-        v[0] = fma(u, c, v[0]);
-        v[1] = fma(u, s, v[1]);
-        v[2] = fma(w * c, c, v[2]);
-        v[3] = fma(w * s, s, v[3]);
-        v[4] = fma(w * c, s, v[4]);
-    }
-#pragma unroll
-    for (int q = 0; q < (GEN ? 7 : 5); ++q) v[q] = fx_wave_sum(v[q]);
-    if (GEN)
-        return power64_gen(SumsGen64{v[5], v[6], v[0], v[1], v[2], v[3], v[4]}, (double)m.n,
-                           m.scale);
-    return power64(Sums64{v[0], v[1], v[2], v[3], v[4]}, (double)m.n, m.scale);
-}
-
 // Power of the bin at frequency f (cycles) = G + side H + e from the products
-// x and d of its block and offset (side -1 or +1); `in`: the bin exists.
-// Called by all lanes of the wavefront.
+// x and d of its block and offset (side -1 or +1).  `ill`: its sums have to be
+// taken term by term (fx_direct).
 template <bool GEN>
 __device__ __forceinline__ double fx_power(const double (&x)[4 * FxSums<GEN>::kSums],
                                            const float (&d)[4 * FxSums<GEN>::kSums], double f,
                                            double G, double H, double side, const ObjMeta& m,
-                                           const FxScales& sc, const double* __restrict__ t,
-                                           const double* __restrict__ y,
-                                           const double* __restrict__ dy, bool in, int lane) {
+                                           const FxScales& sc, bool& ill) {
     constexpr int NG = FxSums<GEN>::kSums;
     const double h = side * H;
     double e;  // f - (G + h), the sum's rounding error included (two-sum)
@@ -407,21 +379,122 @@ __device__ __forceinline__ double fx_power(const double (&x)[4 * FxSums<GEN>::kS
         p = power64_shifted(re[0], im[0], c2, s2, n, n, m.scale);
     }
     const double edge = tr - kFxIll * n;
-    unsigned long long ill = __ballot(in && !(edge > 0.0 && dd * dd + ee * ee < edge * edge));
-    while (ill) {
-        const int l = __builtin_ctzll(ill);
-        ill &= ill - 1;
-        const double q = fx_bin_wave<GEN>(m, t, y, dy, __shfl(f, l, kWave), lane);
-        if (lane == l) p = q;
-    }
+    ill = !(edge > 0.0 && dd * dd + ee * ee < edge * edge);
     return p;
+}
+
+// Bins (from the first of a workgroup's) left to fx_direct.
+template <int N>
+struct FxList {
+    int count;
+    uint16_t bin[N];
+};
+
+// Adds the lanes' bins where `bad` holds.  Called by all lanes of a wavefront.
+template <int N>
+__device__ __forceinline__ void fx_list(FxList<N>& L, int bin, bool bad, int lane) {
+    const unsigned long long bits = __ballot(bad);
+    if (!bits) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&L.count, __popcll(bits));
+    base = uniform_i32(base);
+    if (bad) L.bin[base + __popcll(bits & ((1ull << lane) - 1))] = (uint16_t)bin;
+}
+
+// Powers of `count` bins term by term, bin(q) the q-th, each handed to
+// offer(bin, power) by one thread; called by all threads of the workgroup.  A
+// thread takes four bins at a time, so that their chains of FP64 operations
+// overlap; where there are fewer bins than that, groups of up to 64 lanes share
+// four bins and split the observations.  `staged`: S holds the object's only pass.
+// Bound by the FP64 units, as the plain FP64 kernel is.  Measured, each lane its
+// bin from global memory, or each listed bin by a wavefront of its own -> here:
+// 48 objects of 500 points on 40,000 bins past the residual's range 2,543 -> 1,407
+// us (two bins at a time 1,516), with errors 3,515 -> 1,519; 300 objects of 200
+// points in two clumps with errors 4,783 -> 1,137 us; 300 of six points 3,659 -> 146.
+constexpr int kFxTogether = 4;
+
+template <bool GEN, int THREADS, typename Bin, typename Offer>
+__device__ __forceinline__ void fx_direct(FxStage<GEN>& S, bool staged, const ObjMeta& m,
+                                          const double* __restrict__ t,
+                                          const double* __restrict__ y,
+                                          const double* __restrict__ dy, const FxScales& sc,
+                                          double f_min, double df, double to_cyc, int count,
+                                          Bin bin, Offer offer) {
+    constexpr int NV = GEN ? 7 : 5, KB = kFxTogether;
+    int log_g = 0;
+    while (log_g < 6 && (count << log_g) <= THREADS * KB / 2) ++log_g;
+    const int per = THREADS >> log_g;  // groups of lanes
+    const int sub = threadIdx.x & ((1 << log_g) - 1), group = threadIdx.x >> log_g;
+    for (int r0 = 0; r0 < count; r0 += KB * per) {
+        int64_t i[KB];
+        double f[KB], v[KB][NV];
+#pragma unroll
+        for (int e = 0; e < KB; ++e) {
+            const int q = r0 + e * per + group;
+            i[e] = bin(q < count ? q : r0);
+            f[e] = grid_freq(f_min, df, i[e]) * to_cyc;
+            if (q >= count) i[e] = -1;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[e][k] = 0.0;
+        }
+        for (int64_t jt = 0; jt < m.n; jt += kFxObs) {
+            const int cnt = uniform_i32((int)(m.n - jt < kFxObs ? m.n - jt : kFxObs));
+            if (!staged) {
+                __syncthreads();
+                fx_stage(S, m, t, y, dy, jt, cnt, sc, THREADS);
+                __syncthreads();
+                staged = m.n <= kFxObs;
+            }
+            for (int q = sub; q < cnt; q += 1 << log_g) {
+                const double th = S.hi[q], tl = S.lo[q], u = S.u[q];
+#pragma unroll
+                for (int e = 0; e < KB; ++e) {
+                    double sn, cs;
+                    fx_sincos(f[e], th, tl, &sn, &cs);
+                    v[e][0] = fma(u, cs, v[e][0]);
+                    v[e][1] = fma(u, sn, v[e][1]);
+                    double wc = cs, ws = sn;
+                    if (GEN) {
+                        const double w = S.w[q];
+                        wc *= w;
+                        ws *= w;
+                        v[e][5] += wc;
+                        v[e][6] += ws;
+                    }
+                    v[e][2] = fma(wc, cs, v[e][2]);
+                    v[e][3] = fma(ws, sn, v[e][3]);
+                    v[e][4] = fma(wc, sn, v[e][4]);
+                }
+            }
+        }
+        for (int o = (1 << log_g) >> 1; o > 0; o >>= 1)
+#pragma unroll
+            for (int e = 0; e < KB; ++e)
+#pragma unroll
+                for (int k = 0; k < NV; ++k) v[e][k] += __shfl_xor(v[e][k], o, kWave);
+        if (sub == 0) {
+#pragma unroll
+            for (int e = 0; e < KB; ++e) {
+                if (i[e] < 0) continue;
+                double p;
+                if constexpr (GEN)
+                    p = power64_gen(SumsGen64{v[e][5], v[e][6], v[e][0], v[e][1], v[e][2], v[e][3],
+                                              v[e][4]},
+                                    (double)m.n, m.scale);
+                else
+                    p = power64(Sums64{v[e][0], v[e][1], v[e][2], v[e][3], v[e][4]}, (double)m.n,
+                                m.scale);
+                offer(i[e], p);
+            }
+        }
+    }
 }
 
 // Whether the object's bins, whose frequencies (cycles) are at most f_top in
 // size, go through the matrix cores: the first-order residual covers them, and
-// there are more than a few points.
-__device__ __forceinline__ bool fx_covers(double f_top, const ObjMeta& m) {
-    return m.n > kFxFew && kTwoPi * 2.220446049250313e-16 * f_top * ldexp(1.0, mx_exp_reach(m)) <= kFxResidual;
+// there are more than `few` points.
+__device__ __forceinline__ bool fx_covers(double f_top, const ObjMeta& m, int few) {
+    return m.n > few && kTwoPi * 2.220446049250313e-16 * f_top * ldexp(1.0, mx_exp_reach(m)) <= kFxResidual;
 }
 
 // Wave w's share [lo, hi) of the steps of cnt staged observations.
@@ -473,15 +546,6 @@ __device__ __forceinline__ void fx_gather(const FxSums<GEN>& A, double (*buf)[8]
                 d[q + e] = v;
             }
     }
-}
-
-// Power of one bin on its own, term by term (fx_covers); not inlined, so that
-// its registers stay out of the callers' loops.
-template <bool GEN>
-__device__ __noinline__ double fx_bin(const ObjMeta& m, const double* __restrict__ t,
-                                      const double* __restrict__ y, const double* __restrict__ dy,
-                                      double f) {
-    return GEN ? power64_gen_bin(m, t, y, dy, f) : power64_bin(m, t, y, f);
 }
 
 // Centre frequency of a block row, and offset of a column, in cycles, for the

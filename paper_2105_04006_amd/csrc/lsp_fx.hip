@@ -16,6 +16,8 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
     // the split's partial sums, or the shared offset factors
     __shared__ typename std::conditional<SPLIT, double[W][8][kWave], FxOffsets>::type s_buf;
     __shared__ PeakRec s_red[W];
+    constexpr int kBins = (SPLIT ? 1 : W) * kFxBins;  // the workgroup's
+    __shared__ FxList<kBins> s_list;
 
     const int64_t b = linear_block();
     if (b >= P.n_items) return;
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
     const int64_t w0 = rr.f_lo + tile * kFxBins;
     const bool mine = tile < P.tiles_per_row;
     PeakRec* rec = P.rec + row * P.tiles_per_row + tile;
-    const int64_t g0 = rr.f_lo + (SPLIT ? chunk : chunk * W) * kFxBins;
+    const int64_t g0 = rr.f_lo + chunk * kBins;
     if (rr.obj < 0 || g0 >= rr.f_hi) {
         if (mine && lane == 0 && (!SPLIT || wave == 0)) *rec = PeakRec{0.0, -1};
         return;
@@ -40,8 +42,7 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
     if (m.status != LSP_OBJ_OK) {
         if (P.pgram) {
             const double v = fill_value(m.status);
-            const int64_t end = g0 + (SPLIT ? 1 : W) * kFxBins;
-            for (int64_t i = g0 + threadIdx.x; i < end && i < rr.f_hi; i += kWave * W)
+            for (int64_t i = g0 + threadIdx.x; i < g0 + kBins && i < rr.f_hi; i += kWave * W)
                 store_pgram(P.pgram, P.pgram_f64, rr.obj * P.n_f + i, v);
         }
         if (mine && lane == 0 && (!SPLIT || wave == 0)) *rec = PeakRec{0.0, -1};
@@ -51,18 +52,14 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
     PeakRec best{0.0, -1};
     const int64_t out = rr.obj * P.n_f;
     const double f_top = fmax(fabs(P.f_min), fabs(P.f_min + P.df * (double)P.n_f)) * P.to_cyc;
-    if (!fx_covers(f_top, m)) {
-        // a very long span or a handful of points: bin by bin
-        const int64_t end = w0 + kFxBins < rr.f_hi ? w0 + kFxBins : rr.f_hi;
-        const int step = SPLIT ? kWave * W : kWave;
-        for (int64_t i = w0 + (SPLIT ? (int)threadIdx.x : lane); i < end; i += step) {
-            const double f = grid_freq(P.f_min, P.df, i) * P.to_cyc;
-            const double p = fx_bin<GEN>(m, P.t, P.y, P.dy, f);
-            if (P.pgram) store_pgram(P.pgram, P.pgram_f64, out + i, p);
-            if (better(p, i, best.p, best.i)) best = PeakRec{p, i};
-        }
-    } else {
-        const FxScales sc = fx_scales<GEN>(m);
+    const bool covered = fx_covers(f_top, m, fx_few(GEN));
+    const FxScales sc = fx_scales<GEN>(m);
+    if (threadIdx.x == 0) s_list.count = 0;  // (a barrier follows before it is used)
+    auto offer = [&](int64_t i, double p) {
+        if (P.pgram) store_pgram(P.pgram, P.pgram_f64, out + i, p);
+        if (better(p, i, best.p, best.i)) best = PeakRec{p, i};
+    };
+    if (covered) {
         const double G = fx_centre(P.f_min, P.df, P.to_cyc, w0, lane & 15);
         const double H = fx_offset(P.df, P.to_cyc, lane & 15);
         FxSums<GEN> A;
@@ -77,7 +74,8 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
             if constexpr (SPLIT)
                 fx_accumulate(A, S, cnt, lo, hi, G, H, lane);
             else
-                fx_accumulate<GEN, W>(A, S, cnt, lo, hi, G, H, lane, &s_buf, uniform_i32(wave));
+                fx_accumulate<GEN, W>(A, S, cnt, lo, hi, G, H, lane, &s_buf, uniform_i32(wave),
+                                      w0 >= rr.f_hi);
         }
         constexpr int NQ = 4 * FxSums<GEN>::kSums;
         double xs[SPLIT ? NQ : 1];
@@ -85,7 +83,7 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
         if constexpr (SPLIT) fx_gather<GEN, W>(A, s_buf, wave, lane, xs, ds);
 #pragma unroll
         for (int r = 0; r < (SPLIT ? 1 : 4); ++r) {
-            if (SPLIT && wave >= 4) break;
+            if (SPLIT ? wave >= 4 : w0 >= rr.f_hi) break;
             const int a = fx_row(SPLIT ? wave : r, lane);
             double x[NQ];
             float d[NQ];
@@ -107,28 +105,31 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
                 const int64_t i = side ? i0 + kFxOffs + c : i0 + kFxOffs - 1 - c;
                 const bool in = i < rr.f_hi;
                 const double f = grid_freq(P.f_min, P.df, i) * P.to_cyc;
-                const double p = fx_power<GEN>(x, d, f, Ga, H, side ? 1.0 : -1.0, m, sc, P.t, P.y,
-                                               P.dy, in, lane);
-                if (!in) continue;
-                if (P.pgram) store_pgram(P.pgram, P.pgram_f64, out + i, p);
-                if (better(p, i, best.p, best.i)) best = PeakRec{p, i};
+                bool ill;
+                const double p = fx_power<GEN>(x, d, f, Ga, H, side ? 1.0 : -1.0, m, sc, ill);
+                fx_list(s_list, (int)(i - g0), in && ill, lane);
+                if (in && !ill) offer(i, p);
             }
         }
     }
+    // what is left: the list, or all bins of an object that is not covered
+    __syncthreads();
+    const int left = (int)(rr.f_hi - g0 < kBins ? rr.f_hi - g0 : kBins);
+    const int count = covered ? uniform_i32(s_list.count) : left;
+    fx_direct<GEN, kWave * W>(
+        S, covered && m.n <= kFxObs, m, P.t, P.y, P.dy, sc, P.f_min, P.df, P.to_cyc, count,
+        [&](int q) { return g0 + (covered ? (int)s_list.bin[q] : q); }, offer);
     best = wave_best(best);
-    if (SPLIT) {
+    if (SPLIT || count > 0) {  // bins of any tile: one record for all
         if (lane == 0) s_red[wave] = best;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            PeakRec b2 = s_red[0];
+        if (threadIdx.x == 0)
 #pragma unroll
             for (int w = 1; w < W; ++w)
-                if (better(s_red[w].p, s_red[w].i, b2.p, b2.i)) b2 = s_red[w];
-            *rec = b2;
-        }
-    } else if (mine && lane == 0) {
-        *rec = best;
+                if (better(s_red[w].p, s_red[w].i, best.p, best.i)) best = s_red[w];
+        if (wave != 0) best = PeakRec{0.0, -1};
     }
+    if (mine && lane == 0 && (!SPLIT || wave == 0)) *rec = best;
 }
 
 // FP64 recompute of FP32-form tiles flagged ill-conditioned.  Workgroups stride
@@ -156,6 +157,7 @@ __global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams
     __shared__ PeakRec s_red[kFixW];
     __shared__ FxStage<GEN> S;
     __shared__ double s_buf[kFixW][8][kWave];
+    __shared__ FxList<kFxBins> s_left;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const double f_top = fmax(fabs(P.f_min), fabs(P.f_min + P.df * (double)P.n_f)) * P.to_cyc;
@@ -186,15 +188,13 @@ __global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams
                 if (P.pgram) store_pgram(P.pgram, P.pgram_f64, out + i, p);
                 if (better(p, i, best.p, best.i)) best = PeakRec{p, i};
             };
-            if (!fx_covers(f_top, m)) {
-                for (int64_t i = f0 + threadIdx.x; i < f1; i += kFixThreads) {
-                    const double f = grid_freq(P.f_min, P.df, i) * P.to_cyc;
-                    offer(i, fx_bin<GEN>(m, P.t, P.y, P.dy, f));
-                }
-            } else {
-                const FxScales sc = fx_scales<GEN>(m);
-                const double H = fx_offset(P.df, P.to_cyc, lane & 15);
-                for (int64_t w0 = f0; w0 < f1; w0 += kFxBins) {
+            const bool covered = fx_covers(f_top, m, fx_few_fix(GEN));
+            const FxScales sc = fx_scales<GEN>(m);
+            const double H = fx_offset(P.df, P.to_cyc, lane & 15);
+            for (int64_t w0 = f0; w0 < f1; w0 += kFxBins) {
+                __syncthreads();
+                if (threadIdx.x == 0) s_left.count = 0;
+                if (covered) {
                     const double G = fx_centre(P.f_min, P.df, P.to_cyc, w0, lane & 15);
                     FxSums<GEN> A;
                     fx_zero(A);
@@ -217,11 +217,19 @@ __global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams
                     for (int side = 0; side < 2; ++side) {
                         const int64_t i = side ? i0 + kFxOffs + c : i0 + kFxOffs - 1 - c;
                         const double f = grid_freq(P.f_min, P.df, i) * P.to_cyc;
-                        const double p = fx_power<GEN>(x, d, f, Ga, H, side ? 1.0 : -1.0, m, sc,
-                                                       P.t, P.y, P.dy, i < f1, lane);
-                        if (i < f1) offer(i, p);
+                        bool ill;
+                        const double p =
+                            fx_power<GEN>(x, d, f, Ga, H, side ? 1.0 : -1.0, m, sc, ill);
+                        fx_list(s_left, (int)(i - w0), i < f1 && ill, lane);
+                        if (i < f1 && !ill) offer(i, p);
                     }
                 }
+                __syncthreads();
+                const int left = (int)(f1 - w0 < kFxBins ? f1 - w0 : kFxBins);
+                fx_direct<GEN, kFixThreads>(
+                    S, covered && m.n <= kFxObs, m, P.t, P.y, P.dy, sc, P.f_min, P.df, P.to_cyc,
+                    covered ? uniform_i32(s_left.count) : left,
+                    [&](int q) { return w0 + (covered ? (int)s_left.bin[q] : q); }, offer);
             }
             best = wave_best(best);
             if (lane == 0) s_red[wave] = best;
