@@ -80,7 +80,10 @@ __global__ __launch_bounds__(kWave* W, 2) void fx_kernel(const MainParams P) {
         constexpr int NQ = 4 * FxSums<GEN>::kSums;
         double xs[SPLIT ? NQ : 1];
         float ds[SPLIT ? NQ : 1];
-        if constexpr (SPLIT) fx_gather<GEN, W>(A, s_buf, wave, lane, xs, ds);
+        if constexpr (SPLIT)
+            fx_gather<GEN, W>(A, s_buf, wave, lane, xs, ds);
+        else
+            fx_turn(A);
 #pragma unroll
         for (int r = 0; r < (SPLIT ? 1 : 4); ++r) {
             if (SPLIT ? wave >= 4 : w0 >= rr.f_hi) break;
