@@ -611,7 +611,8 @@ __global__ __launch_bounds__(kWave* kGW, 2) void mx_gen_tile_kernel(const MainPa
                 for (int q = 0; q < 8; ++q) s_b[buf][wave >> 1][wave & 1][q][lane] = B.q[q];
             }
             __syncthreads();
-            const int todo = slices - s0 < 2 ? slices - s0 : 2;
+            // (a wave past the row's end only makes its share of the factors)
+            const int todo = w0 >= rr.f_hi ? 0 : slices - s0 < 2 ? slices - s0 : 2;
             for (int s = 0; s < todo; ++s) {
                 FragG A;
                 const int j = (s0 + s) * kGSlice + quarter * 8;
