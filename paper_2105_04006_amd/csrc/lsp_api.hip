@@ -8,6 +8,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 
@@ -45,6 +46,8 @@ struct Config {
     int64_t chunks_per_row;
     int64_t n_items;
     int64_t rec_per_group;  // records per group (tile records or combine blocks)
+    int64_t rec_room;       // records per group that the workspace has room for
+    size_t spare;           // bytes that the workspace has on top
     int64_t n_obs;
     bool keys;              // FP32 form, unsplit: per-group peak keys + tile flag bits
     bool lpt;               // rows handed out longest first (lsp_order.hip)
@@ -276,6 +279,8 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
     c->n_obs = n_obs;
     c->rec_per_group = c->split > 1 ? (n_f + kCombineThreads - 1) / kCombineThreads
                                     : c->tiles_per_row * rows.rows_per_group;
+    c->rec_room = c->rec_per_group;
+    c->spare = 0;
     // The FP32 forms merge each group's peak into one 64-bit key whose index
     // field holds 32 bits (peak_key).
     c->keys = c->form == LSP_FORM_FP32P && c->split == 1;
@@ -290,6 +295,24 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
     const double terms = (double)n_obs * (double)n_f * ((double)rows.n_rows / (double)n_obj);
     c->lpt = orderable && (o->order == LSP_ORDER_LPT || (o->order == LSP_ORDER_AUTO && terms >= 1e10));
     return LSP_OK;
+}
+
+// Mean points per object up to which the FP64 form's vector kernel is the
+// faster one.  It takes a row in tiles of 64 to 512 bins, to the row's size; the
+// matrix-core kernels take 512 bins at least, and a fixed time for a tile.
+// Measured (us, vector / matrix, with errors in brackets): 2,000 objects on 128
+// bins, 20 points 31 / 69, 1,000 points 482 / 547; on 256 bins, 20 points 39 / 70,
+// 100 points 108 / 108 (112 / 132), 300 points 277 / 209 (289 / 258); on 512 bins,
+// 20 points 58 / 70 (58 / 79), 100 points 180 / 109 (190 / 132); on 10,000 bins, 4
+// points 299 / 317, 5 points 324 / 266 (6 points 329 / 330, 8 points 394 / 292).
+// Shared tiles: 20 objects on 10,000 bins, 16 points 20 / 27, 24 points 23.5 / 25.7,
+// 32 points 27.2 / 25.9; one object, 10 points 14 / 16, 20 points 16.7 / 16.8.
+double fp64_vector_points(int64_t n_f, bool split, bool gen) {
+    if (split) return 24.0;
+    if (n_f <= 128) return INFINITY;
+    if (n_f <= 256) return gen ? 200.0 : 100.0;
+    if (n_f <= 512) return 32.0;
+    return gen ? 6.0 : 4.0;
 }
 
 // The launch configuration of a call: the vector kernels' shape, or, where
@@ -331,6 +354,14 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     const int64_t tile = !f32 ? kFxTile : method.gen ? kMxTileGen : kMxTile;
     const int64_t tiles = (n_f + tile - 1) / tile;
     if (tiles * rows.rows_per_group > kMaxGrid / rows.n_rows) return LSP_OK;
+    // (room for either kernel's records: which one runs depends on n_obs, and the
+    // workspace must not)
+    c->rec_room = std::max(c->rec_room, tiles * rows.rows_per_group);
+    // a program may size one buffer for both methods from the generalized
+    // call, which has always asked for more than the standard one: keep it so
+    c->spare = method.gen ? kAlign : 0;
+    if (!f32 && (double)n_obs <= (double)rows.n_batch * fp64_vector_points(n_f, split, method.gen))
+        return LSP_OK;
     c->mx = split ? kMxSplit : kMxTiles;
     c->mx_waves = waves;
     c->split = 1;
@@ -352,7 +383,7 @@ Layout layout(int64_t n_obj, const lsp_grid* g, const Rows& rows, const Config& 
     L.meta = off;
     off += align_up((size_t)n_obj * sizeof(ObjMeta));
     L.rec = off;
-    off += c.keys ? 0 : align_up(n_groups * (size_t)c.rec_per_group * sizeof(PeakRec));
+    off += c.keys ? 0 : align_up(n_groups * (size_t)c.rec_room * sizeof(PeakRec));
     // key mode: group keys, tile flag bits and the queue counters back to back,
     // so that one fill clears them
     const size_t n_words = c.keys ? ((size_t)rows.n_rows * (size_t)c.tiles_per_row + 31) / 32 : 0;
@@ -380,10 +411,7 @@ Layout layout(int64_t n_obj, const lsp_grid* g, const Rows& rows, const Config& 
     L.hist = off;
     off += c.lpt ? align_up((size_t)(kOrderBlocks + 1) * kOrderBuckets * sizeof(unsigned int))
                  : 0;
-    // a program may size one buffer for both methods from the generalized
-    // call, which has always asked for more than the standard one: keep it so
-    if (c.gen && c.mx != kMxOff) off += kAlign;
-    L.total = off;
+    L.total = off + c.spare;
     return L;
 }
 
