@@ -503,7 +503,7 @@ __device__ __forceinline__ void fx_direct(FxStage<GEN>& S, bool staged, const Ob
                                           Bin bin, Offer offer) {
     constexpr int NV = GEN ? 7 : 5, KB = kFxTogether;
     int log_g = 0;
-    while (log_g < 6 && (count << log_g) <= THREADS * KB / 2) ++log_g;
+    while (log_g < 6 && (count << log_g) <= THREADS * KB / 2 && (1 << log_g) < m.n) ++log_g;
     const int per = THREADS >> log_g;  // groups of lanes
     const int sub = threadIdx.x & ((1 << log_g) - 1), group = threadIdx.x >> log_g;
     for (int r0 = 0; r0 < count; r0 += KB * per) {
@@ -553,20 +553,28 @@ __device__ __forceinline__ void fx_direct(FxStage<GEN>& S, bool staged, const Ob
             for (int e = 0; e < KB; ++e)
 #pragma unroll
                 for (int k = 0; k < NV; ++k) v[e][k] += __shfl_xor(v[e][k], o, kWave);
-        if (sub == 0) {
+        // the powers, which cost as much as a few terms: a bin for each of the
+        // group's lanes, as far as they go
+        const int share = 1 << log_g < KB ? 1 << log_g : KB;
+#pragma unroll 1
+        for (int j = 0; j < KB; j += share) {
+            int64_t own = i[0];
+            double w[NV];
 #pragma unroll
-            for (int e = 0; e < KB; ++e) {
-                if (i[e] < 0) continue;
-                double p;
-                if constexpr (GEN)
-                    p = power64_gen(SumsGen64{v[e][5], v[e][6], v[e][0], v[e][1], v[e][2], v[e][3],
-                                              v[e][4]},
-                                    (double)m.n, m.scale);
-                else
-                    p = power64(Sums64{v[e][0], v[e][1], v[e][2], v[e][3], v[e][4]}, (double)m.n,
-                                m.scale);
-                offer(i[e], p);
+            for (int k = 0; k < NV; ++k) w[k] = v[0][k];
+#pragma unroll
+            for (int e = 1; e < KB; ++e) {
+                const bool it = j + sub == e;
+                own = it ? i[e] : own;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) w[k] = it ? v[e][k] : w[k];
             }
+            if (sub >= share || own < 0) continue;
+            if constexpr (GEN)
+                offer(own, power64_gen(SumsGen64{w[5], w[6], w[0], w[1], w[2], w[3], w[4]},
+                                       (double)m.n, m.scale));
+            else
+                offer(own, power64(Sums64{w[0], w[1], w[2], w[3], w[4]}, (double)m.n, m.scale));
         }
     }
 }

@@ -146,15 +146,22 @@ constexpr int kFixThreads = 256;
 constexpr int kFixW = kFixThreads / kWave;
 
 // Tiles per workgroup and round.  Flagged tiles come in clumps (an object's low
-// frequencies and aliases).  The generalized form flags many: 300 objects on
-// 200,000 bins take 156 us with 1,024-bin tiles 256 at a time, 78 us with 512-bin
-// tiles 64 at a time (a workgroup's tiles a grid apart: 272 us, the same ones of
-// every object).  The standard form flags few: 64 at a time cost 12,000 bands
-// 7.3 us, 256 at a time 5.0 us.
-constexpr int fix_span(bool gen) { return gen ? 64 : kFixThreads; }
+// frequencies and aliases, or every tile of an object of a few points), so a
+// workgroup's share has to be small; but where few are flagged a workgroup costs
+// more than its tiles.  The generalized form flags many: 300 objects on 200,000
+// bins take 156 us with 1,024-bin tiles 256 at a time, 78 us with 512-bin tiles 64
+// at a time (a workgroup's tiles a grid apart: 272 us, the same ones of every
+// object).  The standard form flags few: 64 at a time cost 12,000 bands (48,000
+// tiles) 7.3 us, 256 at a time 5.0 us; but 2,000 objects of three points (20,000
+// tiles, all flagged) 924 and 2,614 us.
+static int fix_span(const FixupParams& p) {
+    if (p.gen || p.n_tiles < 128 * 256) return 64;
+    return p.n_tiles < 256 * 256 ? 128 : kFixThreads;
+}
 
 template <bool GEN>
-__global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams P, const PeakParams K) {
+__global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams P, const PeakParams K,
+                                                               const int span) {
     __shared__ int64_t s_list[kFixThreads];
     __shared__ int s_count;
     __shared__ PeakRec s_red[kFixW];
@@ -164,13 +171,12 @@ __global__ __launch_bounds__(kFixThreads, 2) void fixup_kernel(const FixupParams
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const double f_top = fmax(fabs(P.f_min), fabs(P.f_min + P.df * (double)P.n_f)) * P.to_cyc;
-    constexpr int kSpan = fix_span(GEN);
-    for (int64_t base = (int64_t)blockIdx.x * kSpan; base < P.n_tiles;
-         base += (int64_t)gridDim.x * kSpan) {
+    for (int64_t base = (int64_t)blockIdx.x * span; base < P.n_tiles;
+         base += (int64_t)gridDim.x * span) {
         if (threadIdx.x == 0) s_count = 0;
         __syncthreads();
         const int64_t mine = base + threadIdx.x;
-        if (threadIdx.x < kSpan && mine < P.n_tiles &&
+        if ((int)threadIdx.x < span && mine < P.n_tiles &&
             ((P.ill_bits[mine >> 5] >> (mine & 31)) & 1u))
             s_list[atomicAdd(&s_count, 1)] = mine;
         __syncthreads();
@@ -266,7 +272,7 @@ constexpr int64_t kMaxLastWg = 256;
 int64_t fx_item_bins(int waves, bool split) { return split ? kFxBins : waves * kFxBins; }
 
 bool fixup_writes_peaks(const FixupParams& p, const PeakParams& k) {
-    return k.n_groups <= kFixThreads && p.n_tiles <= kMaxLastWg * fix_span(p.gen != 0);
+    return k.n_groups <= kFixThreads && p.n_tiles <= kMaxLastWg * fix_span(p);
 }
 
 template <bool GEN>
@@ -288,14 +294,14 @@ hipError_t launch_fx(const MainParams& p, int waves, bool split, hipStream_t s) 
 
 hipError_t launch_fixup(const FixupParams& p, const PeakParams& k, hipStream_t s) {
     if (p.n_tiles <= 0) return hipSuccess;
-    const int span = fix_span(p.gen != 0);
+    const int span = fix_span(p);
     int64_t blocks = (p.n_tiles + span - 1) / span;
     if (blocks > 2048) blocks = 2048;
     const dim3 grid((unsigned)blocks), threads(kFixThreads);
     if (p.gen)
-        hipLaunchKernelGGL(fixup_kernel<true>, grid, threads, 0, s, p, k);
+        hipLaunchKernelGGL(fixup_kernel<true>, grid, threads, 0, s, p, k, span);
     else
-        hipLaunchKernelGGL(fixup_kernel<false>, grid, threads, 0, s, p, k);
+        hipLaunchKernelGGL(fixup_kernel<false>, grid, threads, 0, s, p, k, span);
     return hipGetLastError();
 }
 
