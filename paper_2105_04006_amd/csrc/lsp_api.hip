@@ -53,6 +53,7 @@ struct Config {
     bool lpt;               // rows handed out longest first (lsp_order.hip)
     int mx;                 // matrix-core sums: kMxOff, kMxTiles or kMxSplit
     int mx_waves;           // kMxTiles: waves (2,048-bin tiles) per workgroup
+    int mx_parts;           // kMxSplit, one series: parts of its observations, by workgroup
 };
 
 enum { kMxOff = 0, kMxTiles = 1, kMxSplit = 2 };
@@ -123,6 +124,7 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
     c->gen = method.gen;
     c->mx = kMxOff;
     c->mx_waves = 0;
+    c->mx_parts = 1;
     c->obs = o->obs_read == LSP_OBS_DIRECT ? LSP_OBS_DIRECT : LSP_OBS_LDS;
     c->trig = o->seed_trig == LSP_TRIG_AUTO ? LSP_TRIG_HW : o->seed_trig;
     // The read-path and seed-trig variants exist for the standard FP32 form
@@ -315,6 +317,18 @@ double fp64_vector_points(int64_t n_f, bool split, bool gen) {
     return gen ? 6.0 : 4.0;
 }
 
+// Parts of a single series' observations, by workgroup, where its shared tiles
+// leave most of the chip idle: as many as fill 256 CUs once, of at least 512
+// points.  Measured (us, parts of at least 512 / 1,024 / 2,048 points, and one
+// part): 3,000 points on 2,000 bins 29 / 38 / 51, 53; 20,000 points 54 / 51 / 60, 283;
+// on 120,000 bins 97 / 98 / 97, 286; 100,000 points on 10,000 bins 124, 1,358 (393
+// with the vector kernels' split).  Two workgroups a CU: 20,000 points on 50,000
+// bins 90, one 70.  Up to 64 parts, whose sums' bytes bound the workspace.
+int mx_series_parts(int64_t tiles, int64_t n_obs) {
+    const int64_t parts = std::min<int64_t>(std::min<int64_t>(256 / tiles, n_obs / 512), 64);
+    return parts > 1 ? (int)parts : 1;
+}
+
 // The launch configuration of a call: the vector kernels' shape, or, where
 // every tuning field is left to the library, the matrix-core kernels'
 // (lsp_mx.hip with 1,024-bin fix-up tiles; lsp_fx.hip with 512-bin records).
@@ -364,13 +378,15 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
         return LSP_OK;
     c->mx = split ? kMxSplit : kMxTiles;
     c->mx_waves = waves;
+    if (f32 && split && rows.whole && n_obj == 1)
+        c->mx_parts = mx_series_parts((n_f + bins - 1) / bins, n_obs);
     c->split = 1;
     c->persistent = 0;
     c->tile_freqs = tile;
     c->tiles_per_row = tiles;
     c->tiles_per_item = bins / tile;
     c->chunks_per_row = (n_f + bins - 1) / bins;
-    c->n_items = rows.n_rows * c->chunks_per_row;
+    c->n_items = rows.n_rows * c->chunks_per_row * c->mx_parts;
     c->rec_per_group = tiles * rows.rows_per_group;
     c->keys = f32;
     return LSP_OK;
@@ -396,9 +412,8 @@ Layout layout(int64_t n_obj, const lsp_grid* g, const Rows& rows, const Config& 
     L.zero_words = c.keys ? (off - L.keys) / 4 : 0;
     off = align_up(off);
     L.part = off;
-    off += c.split > 1
-               ? align_up((size_t)c.split * (c.gen ? 6 : 4) * (size_t)g->n_f * sizeof(float))
-               : 0;
+    const size_t parts = (size_t)(c.split > 1 ? c.split : c.mx_parts);
+    off += parts > 1 ? align_up(parts * (c.gen ? 6 : 4) * (size_t)g->n_f * sizeof(float)) : 0;
     // LSP_OBS_DIRECT: per-observation staged values (indexed like t)
     const size_t n_obs = c.obs == LSP_OBS_DIRECT ? (size_t)c.n_obs : 0;
     L.stage_t = off;
@@ -512,13 +527,13 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
     mp.tiles_per_item = c.tiles_per_item;
     mp.chunks_per_row = c.chunks_per_row;
     mp.n_items = c.n_items;
-    mp.n_split = c.split;
+    mp.n_split = c.mx != kMxOff ? c.mx_parts : c.split;
     mp.pgram_f64 = opt.pgram_dtype == LSP_PGRAM_F64;
     mp.pgram = pgram;
     mp.rec = c.keys ? nullptr : at<PeakRec>(ws, L.rec);
     mp.keys = c.keys ? at<unsigned long long>(ws, L.keys) : nullptr;
     mp.ill_bits = c.keys ? at<uint32_t>(ws, L.bits) : nullptr;
-    mp.part = c.split > 1 ? at<float>(ws, L.part) : nullptr;
+    mp.part = mp.n_split > 1 ? at<float>(ws, L.part) : nullptr;
     mp.queue = at<unsigned int>(ws, L.queue);
     mp.persistent = c.persistent;
     mp.wave_split = c.ws;

@@ -77,11 +77,25 @@ __device__ __forceinline__ void* object_pgram(const MainParams& P, int64_t obj) 
                        : static_cast<void*>(static_cast<float*>(P.pgram) + obj * P.n_f);
 }
 
-// Both bins (0: minus, 1: plus the offset) of a block's offset from their eight sums.
+// The sums of one of the two bins (side 0: minus, 1: plus the offset) of a block's
+// offset from its eight products: with y at the cosine and sine, then at 2wt (1/4).
+__device__ __forceinline__ void bin_sums(const float (&v)[8], int side, float (&b)[4]) {
+    const float z = side ? 1.0f : -1.0f;
+    b[0] = fmaf(-z, v[1], v[0]);
+    b[1] = fmaf(z, v[3], v[2]);
+    b[2] = fmaf(-z, v[5], v[4]);
+    b[3] = fmaf(z, v[7], v[6]);
+}
+
+// Both bins' powers.
 __device__ __forceinline__ void pair_power(const Finish& R, const float (&v)[8], float (&p)[2],
                                            bool (&ill)[2]) {
-    p[0] = power_mx(v[0] + v[1], v[2] - v[3], v[4] + v[5], v[6] - v[7], R.n4, R.scale4, ill[0]);
-    p[1] = power_mx(v[0] - v[1], v[2] + v[3], v[4] - v[5], v[6] + v[7], R.n4, R.scale4, ill[1]);
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        float b[4];
+        bin_sums(v, side, b);
+        p[side] = power_mx(b[0], b[1], b[2], b[3], R.n4, R.scale4, ill[side]);
+    }
 }
 
 // Bin of (block a, offset m, side) from the tile's first.
@@ -241,9 +255,21 @@ __global__ __launch_bounds__(kWave* W, 2) void mx_tile_kernel(const MainParams P
     if (lane == 0 && best != 0ull) atomicMax(&P.keys[row / P.rows_per_group], best);
 }
 
+// A workgroup's part of a long series' observations, in whole slices (P.n_split
+// parts, the series' own [0, n) where there is one).
+__device__ __forceinline__ void part_range(const MainParams& P, int64_t n, int part, int slice,
+                                           int64_t* lo, int64_t* hi) {
+    const int64_t slices = (n + slice - 1) / slice;
+    const int64_t per = (slices + P.n_split - 1) / P.n_split * slice;
+    *lo = part * per < n ? part * per : n;
+    *hi = *lo + per < n ? *lo + per : n;
+}
+
 // One 32 x 32 tile per workgroup of eight waves, which share out the
 // observations in slices and add their sums through LDS in wave order: for
-// calls whose tiles alone are too few to fill the chip.
+// calls whose tiles alone are too few to fill the chip.  Where even so there are
+// few workgroups and the one series is long, its observations are split over
+// P.n_split of them too, which leave their bins' sums for mx_combine_kernel.
 constexpr int kSplitW = 8;
 constexpr int kSplitObs = 1024;  // observations staged per pass
 
@@ -256,8 +282,9 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
 
     const int64_t b = linear_block();
     if (b >= P.n_items) return;
-    const int64_t rank = b / P.chunks_per_row;
-    const int64_t chunk = b - rank * P.chunks_per_row;
+    const int part = P.n_split > 1 ? (int)(b / P.chunks_per_row) : 0;
+    const int64_t rank = P.n_split > 1 ? 0 : b / P.chunks_per_row;
+    const int64_t chunk = b - (P.n_split > 1 ? part : rank) * P.chunks_per_row;
     const int64_t row = item_row(P.row_perm, rank);
     const RowRange rr =
         decode_row(P.row_obj, P.row_band, P.band_bins, P.rows_per_group, P.n_obj, P.n_f, row);
@@ -265,7 +292,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
     if (rr.obj < 0 || w0 >= rr.f_hi) return;
     const ObjMeta m = P.meta[rr.obj];
     if (m.status != LSP_OBJ_OK) {
-        fill_bins(P, rr, m.status, w0, w0 + kWaveBins, kWave * kSplitW);
+        if (P.n_split == 1) fill_bins(P, rr, m.status, w0, w0 + kWaveBins, kWave * kSplitW);
         return;
     }
     const int lane = threadIdx.x & (kWave - 1);
@@ -281,8 +308,10 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[q][r] = 0.0f;
 
-    for (int64_t jt = 0; jt < m.n; jt += kSplitObs) {
-        const int cnt = (int)(m.n - jt < kSplitObs ? m.n - jt : kSplitObs);
+    int64_t j_lo, j_hi;
+    part_range(P, m.n, part, kSlice, &j_lo, &j_hi);
+    for (int64_t jt = j_lo; jt < j_hi; jt += kSplitObs) {
+        const int cnt = (int)(j_hi - jt < kSplitObs ? j_hi - jt : kSplitObs);
         const int slices = (cnt + kSlice - 1) / kSlice;
         __syncthreads();
         for (int q = threadIdx.x; q < slices * kSlice; q += kWave * kSplitW) {
@@ -318,6 +347,26 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
     }
 
     const Finish R = make_finish(P, m, rr, w0);
+    if (P.n_split > 1) {
+        float* const out = P.part + (int64_t)part * 4 * P.n_f + w0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int r = 2 * wave + e;
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = sum[q][e];
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const int bin = tile_bin(8 * (r / 4) + 4 * half + (r & 3), sub, side);
+                float b4[4];
+                bin_sums(v, side, b4);
+                if (bin < R.left)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) out[q * P.n_f + bin] = b4[q];
+            }
+        }
+        return;
+    }
     LaneBest lb;
     bool ill = false;
     float p[2][2];
@@ -476,12 +525,25 @@ __device__ __forceinline__ FinishG make_finish_g(const MainParams& P, const ObjM
 }
 
 // One of the two bins of an offset: the centre minus (side 0) or plus (side 1) it.
+// Its sums of w, of w yw and (four times the products) of w at 2wt.
+__device__ __forceinline__ void bin_sums_g(const float (&v)[12], int side, float (&b)[6]) {
+    const float z = side ? 1.0f : -1.0f;
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        b[2 * g] = (g == 2 ? 4.0f : 1.0f) * fmaf(-z, v[4 * g + 1], v[4 * g]);
+        b[2 * g + 1] = (g == 2 ? 4.0f : 1.0f) * fmaf(z, v[4 * g + 3], v[4 * g + 2]);
+    }
+}
+
+__device__ __forceinline__ float sums_power_g(const FinishG& R, const float (&b)[6], bool& ill) {
+    return power_mx_gen(b[0], b[1], b[2], b[3], b[4], b[5], R.n, R.rn, R.scale, ill);
+}
+
 __device__ __forceinline__ float bin_power_g(const FinishG& R, const float (&v)[12], int side,
                                              bool& ill) {
-    const float z = side ? 1.0f : -1.0f;
-    return power_mx_gen(fmaf(-z, v[1], v[0]), fmaf(z, v[3], v[2]), fmaf(-z, v[5], v[4]),
-                        fmaf(z, v[7], v[6]), 4.0f * fmaf(-z, v[9], v[8]),
-                        4.0f * fmaf(z, v[11], v[10]), R.n, R.rn, R.scale, ill);
+    float b[6];
+    bin_sums_g(v, side, b);
+    return sums_power_g(R, b, ill);
 }
 
 // Stage observations [jt, jt + cnt) of the object, padded with zeros to whole slices.
@@ -651,8 +713,9 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
 
     const int64_t b = linear_block();
     if (b >= P.n_items) return;
-    const int64_t rank = b / P.chunks_per_row;
-    const int64_t chunk = b - rank * P.chunks_per_row;
+    const int part = P.n_split > 1 ? (int)(b / P.chunks_per_row) : 0;
+    const int64_t rank = P.n_split > 1 ? 0 : b / P.chunks_per_row;
+    const int64_t chunk = b - (P.n_split > 1 ? part : rank) * P.chunks_per_row;
     const int64_t row = item_row(P.row_perm, rank);
     const RowRange rr =
         decode_row(P.row_obj, P.row_band, P.band_bins, P.rows_per_group, P.n_obj, P.n_f, row);
@@ -660,7 +723,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
     if (rr.obj < 0 || w0 >= rr.f_hi) return;
     const ObjMeta m = P.meta[rr.obj];
     if (m.status != LSP_OBJ_OK) {
-        fill_bins(P, rr, m.status, w0, w0 + kGBins, kWave * kSplitW);
+        if (P.n_split == 1) fill_bins(P, rr, m.status, w0, w0 + kGBins, kWave * kSplitW);
         return;
     }
     const int lane = threadIdx.x & (kWave - 1);
@@ -677,8 +740,10 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
 #pragma unroll
         for (int q = 0; q < 12; ++q) acc[h][q] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 
-    for (int64_t jt = 0; jt < m.n; jt += kGSplitObs) {
-        const int cnt = (int)(m.n - jt < kGSplitObs ? m.n - jt : kGSplitObs);
+    int64_t j_lo, j_hi;
+    part_range(P, m.n, part, kGSlice, &j_lo, &j_hi);
+    for (int64_t jt = j_lo; jt < j_hi; jt += kGSplitObs) {
+        const int cnt = (int)(j_hi - jt < kGSplitObs ? j_hi - jt : kGSplitObs);
         const int slices = (cnt + kGSlice - 1) / kGSlice;
         __syncthreads();
         stage_g(P, m, jt, cnt, slices * kGSlice, up_w, up_y, s_tau, s_w, s_wy, kWave * kSplitW);
@@ -711,6 +776,19 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
     }
     // wave w: accumulator row w / 2 of the lane's four, offset half w % 2
     const FinishG R = make_finish_g(P, m, rr, w0);
+    if (P.n_split > 1) {
+        float* const out = P.part + (int64_t)part * 6 * P.n_f + w0;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int bin = tile_bin(4 * quarter + (wave >> 1), 16 * (wave & 1) + sub, side);
+            float b6[6];
+            bin_sums_g(sum, side, b6);
+            if (bin < R.out.left)
+#pragma unroll
+                for (int q = 0; q < 6; ++q) out[q * P.n_f + bin] = b6[q];
+        }
+        return;
+    }
     LaneBest lb;
     bool ill = false;
 #pragma unroll
@@ -742,6 +820,66 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_gen_split_kernel(const M
     }
 }
 
+// Adds the parts' sums of a single series in their order and finishes the bins,
+// a workgroup per fix-up tile.
+constexpr int kCombThreads = 256;
+
+template <bool GEN>
+__global__ __launch_bounds__(kCombThreads) void mx_combine_kernel(const MainParams P) {
+    constexpr int kTileBins = GEN ? kFixG : kFix, kPer = kTileBins / kCombThreads;
+    constexpr int kSums = GEN ? 6 : 4;
+    __shared__ unsigned long long s_key[kCombThreads / kWave];
+    const RowRange rr = decode_row(P.row_obj, P.row_band, P.band_bins, P.rows_per_group, P.n_obj,
+                                   P.n_f, 0);
+    const int64_t w0 = (int64_t)blockIdx.x * kTileBins;
+    const ObjMeta m = P.meta[0];
+    if (m.status != LSP_OBJ_OK) {
+        fill_bins(P, rr, m.status, w0, w0 + kTileBins, kCombThreads);
+        return;
+    }
+    bool ill = false;
+    LaneBest lb;
+    float p[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int bin = k * kCombThreads + (int)threadIdx.x;
+        const bool in = w0 + bin < P.n_f;
+        const float* at = P.part + w0 + (in ? bin : 0);
+        float b[kSums];
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) b[q] = 0.0f;
+#pragma unroll 4
+        for (int s = 0; s < P.n_split; ++s, at += kSums * P.n_f)
+#pragma unroll
+            for (int q = 0; q < kSums; ++q) b[q] += at[q * P.n_f];
+        bool bad;
+        if constexpr (GEN) {
+            p[k] = sums_power_g(make_finish_g(P, m, rr, w0), b, bad);
+        } else {
+            const Finish R = make_finish(P, m, rr, w0);
+            p[k] = power_mx(b[0], b[1], b[2], b[3], R.n4, R.scale4, bad);
+        }
+        ill |= bad && in;
+        lb.offer(in ? p[k] : -1.0f, bin);
+    }
+    Finish R = make_finish(P, m, rr, w0);
+    R.left = (int)(P.n_f - w0 < kTileBins ? P.n_f - w0 : kTileBins);
+    if (R.pgram)
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) R.store(w0, k * kCombThreads + (int)threadIdx.x, p[k]);
+    const unsigned long long key = wave_key(lb, w0);
+    if ((threadIdx.x & (kWave - 1)) == 0) s_key[threadIdx.x / kWave] = key;
+    const bool any = __syncthreads_or(ill);
+    if (threadIdx.x != 0) return;
+    if (any) {
+        atomicOr(&P.ill_bits[blockIdx.x >> 5], 1u << (blockIdx.x & 31));
+        return;
+    }
+    unsigned long long best = 0ull;
+    for (int w = 0; w < kCombThreads / kWave; ++w) best = umax64(best, s_key[w]);
+    if (best != 0ull) atomicMax(&P.keys[0], best);
+}
+
 }  // namespace
 
 int64_t mx_item_bins(int waves, bool split, bool gen) {
@@ -752,6 +890,22 @@ int64_t mx_item_bins(int waves, bool split, bool gen) {
 hipError_t launch_mx(const MainParams& p, int waves, bool split, hipStream_t s) {
     if (p.n_items <= 0) return hipSuccess;
     const dim3 grid = grid_for(p.n_items);
+    if (p.n_split > 1) {
+        // one series, at most a few hundred tiles
+        if (!split) return hipErrorInvalidValue;
+        if (p.gen)
+            hipLaunchKernelGGL(mx_gen_split_kernel, grid, dim3(kWave * kSplitW), 0, s, p);
+        else
+            hipLaunchKernelGGL(mx_split_kernel, grid, dim3(kWave * kSplitW), 0, s, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const dim3 tiles((unsigned)p.tiles_per_row), threads(kCombThreads);
+        if (p.gen)
+            hipLaunchKernelGGL(mx_combine_kernel<true>, tiles, threads, 0, s, p);
+        else
+            hipLaunchKernelGGL(mx_combine_kernel<false>, tiles, threads, 0, s, p);
+        return hipGetLastError();
+    }
     if (p.gen) {
         if (split)
             hipLaunchKernelGGL(mx_gen_split_kernel, grid, dim3(kWave * kSplitW), 0, s, p);
