@@ -187,16 +187,30 @@ __device__ __forceinline__ void accumulate(f16v (&acc)[8], const Frag& A, const 
         }
 }
 
+// The factor from the power in scaled magnitudes to the reported one, in two
+// parts: unnormalised powers of magnitudes of 1e-18 are ordinary floats, the
+// factor is not.  The first is a power of two, so a power that needs one part
+// rounds as it would with the whole factor.
+struct PowerScale {
+    float two, rest;
+};
+
+__device__ __forceinline__ PowerScale power_scale(double f) {
+    const int e = f > 0.0 ? ilogb(f) / 2 : 0;
+    return PowerScale{(float)ldexp(1.0, e), (float)ldexp(f, -e)};
+}
+
 // Power of one bin from its sums, the double-angle sums at 1/4 (power32 with
 // N/4 for N): P = (A N - B R) / (N^2 - R^2), `ill` as in power32.
 __device__ __forceinline__ float power_mx(float xc, float xs, float c2, float s2, float n4,
-                                          float scale4, bool& ill) {
+                                          PowerScale scale4, bool& ill) {
     const float r2 = fmaf(c2, c2, s2 * s2);
     const float n2 = n4 * n4;
     ill = !(r2 < (1.0f - kIllTheta) * (1.0f - kIllTheta) * n2);
     const float a = fmaf(xc, xc, xs * xs);
     const float br = fmaf(fmaf(xc, xc, -(xs * xs)), c2, 2.0f * xc * xs * s2);
-    return fmaxf(fmaf(a, n4, -br), 0.0f) * __builtin_amdgcn_rcpf(n2 - r2) * scale4;
+    return fmaxf(fmaf(a, n4, -br), 0.0f) * __builtin_amdgcn_rcpf(n2 - r2) * scale4.two *
+           scale4.rest;
 }
 
 }  // namespace mx

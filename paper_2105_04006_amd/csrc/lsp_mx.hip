@@ -57,7 +57,8 @@ __device__ __forceinline__ unsigned long long wave_key(const LaneBest& b, int64_
 }
 
 struct Finish {
-    float n4, scale4;
+    float n4;
+    PowerScale scale4;
     void* pgram;   // periodogram at the object's first bin, or NULL
     int32_t f64;
     int left;      // the row's bins from the tile's first, at most a tile
@@ -108,7 +109,7 @@ __device__ __forceinline__ Finish make_finish(const MainParams& P, const ObjMeta
     Finish R;
     const double back = ldexp(1.0, -mx_exp_y(m));
     R.n4 = 0.25f * (float)m.n;
-    R.scale4 = (float)(0.25 * (m.scale * back * back));
+    R.scale4 = power_scale(0.25 * (m.scale * back * back));
     R.pgram = object_pgram(P, rr.obj);
     R.f64 = P.pgram_f64;
     R.left = (int)(rr.f_hi - w0 < kWaveBins ? rr.f_hi - w0 : kWaveBins);
@@ -493,7 +494,7 @@ __device__ __forceinline__ void accumulate_g(f4v (&acc)[12], const FragG& A, con
 // square root.  `ill` as there: T - R <= n/32.  c2, s2 are sum w cos 2wt and
 // sum w sin 2wt.
 __device__ __forceinline__ float power_mx_gen(float c1, float s1, float yc, float ys, float c2,
-                                              float s2, float n, float rn, float scale,
+                                              float s2, float n, float rn, PowerScale scale,
                                               bool& ill) {
     const float tr = fmaf(-rn, fmaf(c1, c1, s1 * s1), n);
     const float d = fmaf(-rn, fmaf(c1, c1, -(s1 * s1)), c2);
@@ -503,11 +504,13 @@ __device__ __forceinline__ float power_mx_gen(float c1, float s1, float yc, floa
     ill = !(edge > 0.0f && r2 < edge * edge);
     const float q = fmaf(yc, yc, ys * ys);
     const float t = fmaf(fmaf(yc, yc, -(ys * ys)), d, 2.0f * yc * ys * e);
-    return fmaxf(fmaf(q, tr, -t), 0.0f) * __builtin_amdgcn_rcpf(fmaf(tr, tr, -r2)) * scale;
+    return fmaxf(fmaf(q, tr, -t), 0.0f) * __builtin_amdgcn_rcpf(fmaf(tr, tr, -r2)) * scale.two *
+           scale.rest;
 }
 
 struct FinishG {
-    float n, rn, scale;
+    float n, rn;
+    PowerScale scale;
     Finish out;
 };
 
@@ -517,7 +520,7 @@ __device__ __forceinline__ FinishG make_finish_g(const MainParams& P, const ObjM
     const double up_w = ldexp(1.0, mx_exp_w(m)), back = ldexp(1.0, -mx_exp_y(m));
     R.n = (float)((double)m.n * up_w);
     R.rn = (float)(1.0 / ((double)m.n * up_w));
-    R.scale = (float)(m.scale * back * back * up_w);
+    R.scale = power_scale(m.scale * back * back * up_w);
     R.out.pgram = object_pgram(P, rr.obj);
     R.out.f64 = P.pgram_f64;
     R.out.left = (int)(rr.f_hi - w0 < kGBins ? rr.f_hi - w0 : kGBins);
