@@ -904,7 +904,8 @@ static lsp::GemmArgs gemm_args(int64_t M, int64_t N, int64_t K, const void* A, i
 
 // Launches the first n products of G (with G.s where G.s.c > 0) with one tile
 // size: 128 x 128 where it gives two workgroups per CU, 64 x 64 where it gives
-// one for every other CU, else 32 x 32.  Measured (us):
+// one for every other CU, else 32 x 32; neither larger one where half of it would
+// lie outside a product.  Measured (us):
 //   rows x K x columns     128 tiles    64 tiles    32 tiles
 //   20,000 x 1,088 x 512   628:  44   2,504:  52        113
 //   20,000 x 512 x 256     314:  18.6 1,252:  18         34
@@ -912,6 +913,9 @@ static lsp::GemmArgs gemm_args(int64_t M, int64_t N, int64_t K, const void* A, i
 //   1,088 x 512 x 512                   136:   6.9  544:  8.3
 //   512 x 512 x 256 + 512 x 256 x 512    96:   7.1  384:  6.2
 //   512 x 1,088 x 512                    64:  10.2  256:  9.2
+//   100,000 x 64 x 64      782:  23.6 1,563:  12.0
+//   64 x 64 x 200,000    1,563:  39.3 3,125:  19.1
+//   100,000 x 64 x 32      782:  15.7 1,563:  13.8  3,125:  10.2
 static lsp_status launch_group(lsp::GemmGroup& G, int n, void* stream) {
     for (int q = 0; q < n; ++q)
         if ((G.g[q].M + 63) / 64 > 65535 || (G.g[q].N + 63) / 64 > 65535) return LSP_EUNSUPPORTED;
@@ -943,7 +947,15 @@ static lsp_status launch_group(lsp::GemmGroup& G, int n, void* stream) {
         }
         return LSP_OK;
     }
-    const int t = general ? 64 : count(128) >= 512 ? 128 : count(64) >= 128 ? 64 : 32;
+    bool narrow = false, slim = false;
+    for (int q = 0; q < n; ++q) {
+        narrow |= G.g[q].M <= 64 || G.g[q].N <= 64;
+        slim |= G.g[q].M <= 32 || G.g[q].N <= 32;
+    }
+    const int t = general                          ? 64
+                  : !narrow && count(128) >= 512   ? 128
+                  : !slim && count(64) >= 128      ? 64
+                                                   : 32;
     G.blocks = count(t) + sums;
     const dim3 grid = lsp::grid_for(G.blocks), threads(256);
     if (general)
