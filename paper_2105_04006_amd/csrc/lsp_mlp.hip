@@ -380,41 +380,63 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int64_t m0, int64_t
     }
 }
 
-// Column sums of an n x c FP32 matrix, 16 columns per workgroup of 256 threads
-// and 16 row phases (row i goes to phase i mod 16): each thread sums its phase
-// in row order and the 16 phase sums are added in phase order, so the result
-// does not depend on scheduling.
+// Column sums of an n x c FP32 matrix, 16 or 64 columns per workgroup of 256
+// threads and 16 row phases (row i goes to phase i mod 16): a phase is summed in
+// row order by one thread and the 16 phase sums are added in phase order, so the
+// result does not depend on scheduling or on the columns per workgroup.
 struct ColSums {
     const float* x;
     int64_t n;
     int32_t c;
-    int32_t pad;
+    int32_t wide;  // 64 columns per workgroup
     float* out;
 };
 
-constexpr int kSumCols = 16, kSumPhases = 16;
+constexpr int kSumCols = 16, kSumWide = 64, kSumPhases = 16;
 
+// 64 columns give whole cache lines of a row, but where there are not as many
+// workgroups of them as CUs, 16 columns and a phase a thread keep more rows in
+// flight: 100 x 50,000 7.0 us (16 columns 9.5), 1,000 x 20,000 15.0 us (24.7); 100,000
+// x 64 271 us with 16 columns.
+inline bool sum_wide(int64_t c) { return c >= 256 * kSumWide; }
+
+template <int COLS>
 __device__ __forceinline__ void col_sums_block(const ColSums& S, int64_t block, float* lds) {
-    const int tx = threadIdx.x % kSumCols, ph = threadIdx.x / kSumCols;
-    const int64_t j = block * kSumCols + tx;
-    float s = 0.f;
+    constexpr int kRows = 256 / COLS, kPer = kSumPhases / kRows;  // phases per thread
+    const int tx = threadIdx.x % COLS, r = threadIdx.x / COLS;
+    const int64_t j = block * COLS + tx;
+    float s[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) s[k] = 0.f;
     if (j < S.c) {
-        int64_t i = ph;
-        // eight rows in flight, added in order
-        for (; i + 7 * kSumPhases < S.n; i += 8 * kSumPhases) {
-            float v[8];
+        // eight rows in flight, each phase's added in order
+        constexpr int kTurns = 8 / kPer;
+        int64_t i = 0;
+        for (; i + kTurns * kSumPhases <= S.n; i += kTurns * kSumPhases) {
+            float v[kTurns][kPer];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = S.x[(i + q * kSumPhases) * S.c + j];
+            for (int q = 0; q < kTurns; ++q)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) s += v[q];
+                for (int k = 0; k < kPer; ++k)
+                    v[q][k] = S.x[(i + q * kSumPhases + k * kRows + r) * S.c + j];
+#pragma unroll
+            for (int q = 0; q < kTurns; ++q)
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) s[k] += v[q][k];
         }
-        for (; i < S.n; i += kSumPhases) s += S.x[i * S.c + j];
+        for (; i < S.n; i += kSumPhases)
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int64_t row = i + k * kRows + r;
+                if (row < S.n) s[k] += S.x[row * S.c + j];
+            }
     }
-    lds[ph * kSumCols + tx] = s;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) lds[(k * kRows + r) * COLS + tx] = s[k];
     __syncthreads();
-    if (ph == 0 && j < S.c) {
+    if (r == 0 && j < S.c) {
         float t = lds[tx];
-        for (int q = 1; q < kSumPhases; ++q) t += lds[q * kSumCols + tx];
+        for (int q = 1; q < kSumPhases; ++q) t += lds[q * COLS + tx];
         S.out[j] = t;
     }
 }
@@ -439,7 +461,11 @@ __global__ __launch_bounds__(256, 2) void gemm_group_kernel(const GemmGroup G) {
     int64_t b = linear_block();
     if (b >= G.blocks) return;
     if (b >= G.tiles[0] + G.tiles[1]) {
-        col_sums_block(G.s, b - G.tiles[0] - G.tiles[1], reinterpret_cast<float*>(lds));
+        b -= G.tiles[0] + G.tiles[1];
+        if (G.s.wide)
+            col_sums_block<kSumWide>(G.s, b, reinterpret_cast<float*>(lds));
+        else
+            col_sums_block<kSumCols>(G.s, b, reinterpret_cast<float*>(lds));
         return;
     }
     const int which = b >= G.tiles[0];
@@ -928,7 +954,8 @@ static lsp_status launch_group(lsp::GemmGroup& G, int n, void* stream) {
         return all;
     };
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t sums = G.s.c > 0 ? (G.s.c + lsp::kSumCols - 1) / lsp::kSumCols : 0;
+    const int64_t cols = G.s.wide ? lsp::kSumWide : lsp::kSumCols;
+    const int64_t sums = G.s.c > 0 ? (G.s.c + cols - 1) / cols : 0;
     // other load modes (unaligned or strided operands) take the 64 x 64 tile
     bool general = false;
     for (int q = 0; q < n; ++q) {
@@ -1019,7 +1046,7 @@ lsp_status lsp_softmax_xent(const float* logits, const int32_t* labels, int64_t 
 lsp_status lsp_col_sums(const float* x, int64_t n, int32_t c, float* out, void* stream) {
     if (n < 0 || c < 1 || !out || (n > 0 && !x)) return LSP_EINVAL;
     lsp::GemmGroup G = {};
-    G.s = lsp::ColSums{x, n, c, 0, out};
+    G.s = lsp::ColSums{x, n, c, lsp::sum_wide(c), out};
     return launch_group(G, 0, stream);
 }
 
@@ -1155,7 +1182,7 @@ lsp_status lsp_mlp_backward(const lsp_mlp* net, const void* x_bf16, const int32_
         if (dz)
             G.g[1] = gemm_args(n, di, dn, gb, dn, 1, net->w_bf16[l], 1, dn, nullptr, in, 0, dz,
                                dzb, di);
-        G.s = lsp::ColSums{g, n, (int32_t)dn, 0, grads->b[l]};
+        G.s = lsp::ColSums{g, n, (int32_t)dn, lsp::sum_wide(dn), grads->b[l]};
         return launch_group(G, dz ? 2 : 1, stream);
     };
     if ((st = layer(2, h2_bf16, g3, g3b, dz2, dz2b)) != LSP_OK) return st;
