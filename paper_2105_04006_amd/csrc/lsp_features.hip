@@ -81,6 +81,17 @@ __device__ __forceinline__ float pool_halves(float lo, float hi) {
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// The exponent e for which the largest of |u[q .. b)| times 2^e is in [2^13, 2^14),
+// at most 100; the same in every lane.
+__device__ __forceinline__ int run_exp(const float* u, int q, int b, int lane) {
+    float top = 0.0f;
+    for (int j = q + lane; j < b; j += kWave) top = fmaxf(top, fabsf(u[j]));
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, kWave));
+    const int e = 13 + 127 - (uniform_i32(__float_as_int(top)) >> 23);
+    return e < 100 ? e : 100;
+}
+
 // One workgroup per object; a wave owns 2,048 of the 8,192 bins as a 32 x 32
 // tile whose accumulator rows are the offsets and whose columns the blocks, so
 // that a lane holds runs of four neighbouring bins and the pooling is one
@@ -98,6 +109,7 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
     __shared__ float s_u[kTile + kSlice];
     __shared__ h8 s_b[2][kRound][8][kWave];
     __shared__ unsigned long long s_starts[kTile / kWave];  // new-season flags, one bit each
+    __shared__ unsigned long long s_large[kTile / kWave];   // magnitudes of 1 (scaled) and more
 
     const int64_t block = linear_block();
     if (block >= P.n_obj * kCoarseParts) return;
@@ -136,6 +148,9 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
     int ns = 0;
     int64_t g0 = m.j0;
     float syy = 0.0f;
+    // 2^e_group scales the group's magnitudes on top of the object's scale: a group
+    // whose largest one is below 2^-14 of the object's keeps its bits in f16
+    int e_group = 0;
 
     const int64_t j_end = m.j0 + m.n;
     for (int64_t jt = m.j0;; jt += kTile) {
@@ -161,8 +176,11 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
                 }
                 s_tau[q] = tc;
                 s_u[q] = u;
-                const unsigned long long word = __ballot(starts);
-                if (lane == 0) s_starts[r] = word;
+                const unsigned long long word = __ballot(starts), large = __ballot(fabsf(u) >= 1.0f);
+                if (lane == 0) {
+                    s_starts[r] = word;
+                    s_large[r] = large;
+                }
             }
             if (tid < kSlice) {  // a slice may read past the pass
                 s_tau[kTile + tid] = 0.0;
@@ -235,6 +253,7 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
                 }
                 if (over) break;
                 clear();
+                e_group = 0;
                 ns = 0;
                 g0 = jt + q;
                 syy = 0.0f;
@@ -254,6 +273,31 @@ __global__ __launch_bounds__(kWave* kCoarseW, 2) void coarse_kernel(const FeatPa
                     b = w * kWave + (int)__builtin_ctzll(bits);
                     break;
                 }
+            }
+            bool large = false;
+            for (int w = q / kWave; w * kWave < b; ++w) {
+                uint64_t bits = (uint64_t)uniform_i64((int64_t)s_large[w]);
+                if (w == q / kWave) bits &= ~0ull << (q % kWave);
+                if ((w + 1) * kWave > b) bits &= ~(~0ull << (b % kWave));
+                large |= bits != 0ull;
+            }
+            if (!large || e_group != 0) {  // rare
+                const int e = large ? 0 : run_exp(s_u, q, b, lane);
+                if (ns == 0) {
+                    e_group = e;
+                } else if (e < e_group) {
+                    const float down = ldexpf(1.0f, e - e_group);
+                    syy = syy * down * down;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[k][r] *= down;
+                    e_group = e;
+                }
+                const float scale = ldexpf(1.0f, e_group);
+                __syncthreads();
+                for (int j = q + tid; j < b; j += kWave * kCoarseW) s_u[j] *= scale;
+                __syncthreads();
             }
             for (int j = q + lane; j < b; j += kWave) syy = fmaf(s_u[j], s_u[j], syy);
             for (int c0 = q; c0 < b; c0 += kRound * kSlice) {
