@@ -129,6 +129,14 @@ enum {
                             dealt round-robin over the 8 XCDs (lsp_row_order)      */
 };
 
+/* Which kernels take the sums. */
+enum {
+    LSP_KERNELS_AUTO = 0,   /* those of the tuning fields below: see lsp_options          */
+    LSP_KERNELS_MATRIX = 1, /* as if every tuning field were 0                            */
+    LSP_KERNELS_VECTOR = 2  /* the vector kernels, with the library's choices for the
+                               tuning fields left at 0                                    */
+};
+
 /* Work scheduling of the batch path. */
 enum {
     LSP_SCHED_AUTO = 0,
@@ -157,10 +165,12 @@ typedef struct {
  * Options.  A zero-initialised struct means: FP64 form, unnormalised P_LS, y
  * used as given, FP32 periodogram, library-chosen tuning; callers normally
  * start from lsp_default_options().  Tuning fields left at 0 are chosen by the
- * library (built-in heuristics for the shape).  Every form (standard and
- * generalized) runs its matrix-core kernels when k_per_lane, waves_per_wg,
- * t_split, schedule, recurrence, wave_split, obs_read and seed_trig are all 0;
- * a value in any of them describes, and selects, the vector kernels.
+ * library (built-in heuristics for the shape).  When k_per_lane, waves_per_wg,
+ * t_split, schedule, recurrence, wave_split, obs_read and seed_trig are all 0,
+ * every form (standard and generalized) runs its matrix-core kernels, but for
+ * FP64 calls on small grids or of a few points an object, where the vector
+ * kernel is the faster one; a value in any of them describes, and selects, the
+ * vector kernels.  `kernels` overrides that.
  */
 typedef struct {
     int32_t form;          /* LSP_FORM_*                                               */
@@ -177,7 +187,10 @@ typedef struct {
     int32_t obs_read;      /* LSP_OBS_* (FP32 form only)                                */
     int32_t seed_trig;     /* LSP_TRIG_* (FP32 form only)                               */
     int32_t order;         /* LSP_ORDER_* (batches and row mode)                        */
-    int32_t reserved;      /* 0                                                         */
+    union {
+        int32_t kernels;   /* LSP_KERNELS_*; any other value counts as AUTO              */
+        int32_t reserved;  /* its former name                                           */
+    };
 } lsp_options;
 
 /* One object's peak (40 bytes). */
@@ -695,14 +708,16 @@ lsp_status lsp_select_fallback(const lsp_peak *peaks, const float *mass, int64_t
  * lsp_batch; lsp_gen_* when generalized == 1) resolves for this shape and
  * these options: the tuning fields of `opt` left at 0 filled with the
  * library's choices, the bins one frequency tile covers, the consecutive
- * tiles one work item takes and the number of work items.  It is what the
- * call would enqueue on the vector kernels; nothing is launched.  Used to
- * state the K, recurrence and schedule behind a measurement (the work per bin
- * of Section 2 depends on them).  A call with every tuning field at 0 runs the
- * matrix-core kernels instead (see lsp_options), whose shape has no such
- * choices; the shape reported is the one its vector kernels would take.
+ * tiles one work item takes and the number of work items.  Nothing is
+ * launched.  Used to state the K, recurrence and schedule behind a measurement
+ * (the work per bin of Section 2 depends on them).  Where the call would run
+ * the matrix-core kernels, which have no such choices, `kernels` says so, the
+ * shape reported here is the one its vector kernels would take, and
+ * lsp_describe_matrix reports the one it does take.  Either way a call with the
+ * resolved options takes the same kernels.
  *   resolved : host, receives the options with every AUTO / 0 field resolved
- *              (form, normalize, subtract_mean and pgram_dtype as given).
+ *              (form, normalize, subtract_mean and pgram_dtype as given) and
+ *              kernels LSP_KERNELS_MATRIX or LSP_KERNELS_VECTOR.
  *   tile_freqs, tiles_per_item, n_items : host, may be NULL.
  * Errors: LSP_EINVAL / LSP_EUNSUPPORTED as the call itself would return them
  * (NULL grid or resolved, n_obj < 1, n_obs < 0, bad grid or options).
@@ -711,6 +726,24 @@ lsp_status lsp_describe_launch(int64_t n_obj, int64_t n_obs, const lsp_grid *gri
                                const lsp_options *opt, int32_t generalized,
                                lsp_options *resolved, int64_t *tile_freqs,
                                int64_t *tiles_per_item, int64_t *n_items);
+
+/*
+ * The shape of the matrix-core kernels for the same call.
+ * Errors as lsp_describe_launch, and LSP_EUNSUPPORTED where the call runs the
+ * vector kernels.
+ */
+typedef struct {
+    int64_t wave_bins; /* bins of a wavefront's (or of the shared) tile                */
+    int64_t n_items;   /* workgroups                                                  */
+    int32_t waves;     /* wavefronts per workgroup                                    */
+    int32_t shared;    /* 1: they share a tile and split its observations; 0: each
+                          has a tile of its own                                       */
+    int32_t parts;     /* one long series: parts of its observations, by workgroup      */
+    int32_t reserved;
+} lsp_matrix_shape;
+lsp_status lsp_describe_matrix(int64_t n_obj, int64_t n_obs, const lsp_grid *grid,
+                               const lsp_options *opt, int32_t generalized,
+                               lsp_matrix_shape *shape);
 
 /*
  * The longest-first row order the batch calls use with LSP_ORDER_LPT

@@ -299,6 +299,17 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
     return LSP_OK;
 }
 
+lsp_options without_tuning(const lsp_options& o) {
+    lsp_options r = o;
+    r.k_per_lane = r.waves_per_wg = r.t_split = 0;
+    r.schedule = LSP_SCHED_AUTO;
+    r.recurrence = LSP_REC_AUTO;
+    r.wave_split = LSP_WSPLIT_AUTO;
+    r.obs_read = LSP_OBS_AUTO;
+    r.seed_trig = LSP_TRIG_AUTO;
+    return r;
+}
+
 // Mean points per object up to which the FP64 form's vector kernel is the
 // faster one.  It takes a row in tiles of 64 to 512 bins, to the row's size; the
 // matrix-core kernels take 512 bins at least, and a fixed time for a tile.
@@ -332,15 +343,21 @@ int mx_series_parts(int64_t tiles, int64_t n_obs) {
 // The launch configuration of a call: the vector kernels' shape, or, where
 // every tuning field is left to the library, the matrix-core kernels'
 // (lsp_mx.hip with 1,024-bin fix-up tiles; lsp_fx.hip with 512-bin records).
-lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* o,
+lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* given,
                    const Rows& rows, Config* c, const Method& method = Method{}) {
+    lsp_options untuned;
+    const lsp_options* o = given;
+    if (given->kernels == LSP_KERNELS_MATRIX) {
+        untuned = without_tuning(*given);
+        o = &untuned;
+    }
     const lsp_status st = resolve_vector(n_obj, n_obs, g, o, rows, c, method);
     if (st != LSP_OK) return st;
     const bool left = !o->k_per_lane && !o->waves_per_wg && !o->t_split &&
                       o->schedule == LSP_SCHED_AUTO && o->recurrence == LSP_REC_AUTO &&
                       o->wave_split == LSP_WSPLIT_AUTO && o->obs_read == LSP_OBS_AUTO &&
                       o->seed_trig == LSP_TRIG_AUTO;
-    if (!left) return LSP_OK;
+    if (!left || o->kernels == LSP_KERNELS_VECTOR) return LSP_OK;
     const bool f32 = o->form == LSP_FORM_FP32P;
     if (f32 && g->n_f > (int64_t)0xFFFFFFFE) return LSP_OK;
     const int64_t n_f = rows.row_band ? (rows.band_bins < g->n_f ? rows.band_bins : g->n_f) : g->n_f;
@@ -980,9 +997,16 @@ lsp_status lsp_describe_launch(int64_t n_obj, int64_t n_obs, const lsp_grid* gri
     lsp::Method method;
     method.gen = generalized != 0;
     lsp::Config c;
-    st = lsp::resolve_vector(n_obj, n_obs, grid, &opt, lsp::whole_grid(n_obj, grid), &c, method);
+    const lsp::Rows rows = lsp::whole_grid(n_obj, grid);
+    st = lsp::resolve(n_obj, n_obs, grid, &opt, rows, &c, method);
     if (st != LSP_OK) return st;
     lsp_options r = opt;
+    r.kernels = c.mx != lsp::kMxOff ? LSP_KERNELS_MATRIX : LSP_KERNELS_VECTOR;
+    if (c.mx != lsp::kMxOff) {
+        const lsp_options untuned = lsp::without_tuning(opt);
+        st = lsp::resolve_vector(n_obj, n_obs, grid, &untuned, rows, &c, method);
+        if (st != LSP_OK) return st;
+    }
     r.k_per_lane = c.k;
     r.waves_per_wg = c.waves;
     r.t_split = c.split;
@@ -998,6 +1022,30 @@ lsp_status lsp_describe_launch(int64_t n_obj, int64_t n_obs, const lsp_grid* gri
     if (tile_freqs) *tile_freqs = c.tile_freqs;
     if (tiles_per_item) *tiles_per_item = c.tiles_per_item;
     if (n_items) *n_items = c.n_items;
+    return LSP_OK;
+}
+
+lsp_status lsp_describe_matrix(int64_t n_obj, int64_t n_obs, const lsp_grid* grid,
+                               const lsp_options* opt_in, int32_t generalized,
+                               lsp_matrix_shape* shape) {
+    if (!grid || !shape || n_obj < 1 || n_obs < 0 || !lsp::is_bool(generalized)) return LSP_EINVAL;
+    if (!lsp::valid_grid(grid)) return LSP_EINVAL;
+    const lsp_options opt = opt_in ? *opt_in : lsp_default_options();
+    lsp_status st = lsp::valid_options(&opt);
+    if (st != LSP_OK) return st;
+    lsp::Method method;
+    method.gen = generalized != 0;
+    lsp::Config c;
+    st = lsp::resolve(n_obj, n_obs, grid, &opt, lsp::whole_grid(n_obj, grid), &c, method);
+    if (st != LSP_OK) return st;
+    if (c.mx == lsp::kMxOff) return LSP_EUNSUPPORTED;
+    lsp_matrix_shape r = {};
+    r.wave_bins = c.form == LSP_FORM_FP32P ? lsp::mx_item_bins(1, false, method.gen) : lsp::kFxTile;
+    r.n_items = c.n_items;
+    r.waves = c.mx_waves;
+    r.shared = c.mx == lsp::kMxSplit;
+    r.parts = c.mx_parts;
+    *shape = r;
     return LSP_OK;
 }
 

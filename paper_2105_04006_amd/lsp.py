@@ -31,6 +31,7 @@ WSPLIT_AUTO, WSPLIT_OFF, WSPLIT_ON = 0, 1, 2
 OBS_AUTO, OBS_LDS, OBS_DIRECT = 0, 1, 2
 TRIG_AUTO, TRIG_HW, TRIG_LIB, TRIG_POLY = 0, 1, 2, 3
 ORDER_AUTO, ORDER_INPUT, ORDER_LPT = 0, 1, 2
+KERNELS_AUTO, KERNELS_MATRIX, KERNELS_VECTOR = 0, 1, 2
 
 PEAK_DTYPE = np.dtype(
     [("index", "<i8"), ("freq", "<f8"), ("period", "<f8"), ("power", "<f8"),
@@ -51,7 +52,13 @@ class Options(ctypes.Structure):
                 ("t_split", ctypes.c_int32), ("schedule", ctypes.c_int32),
                 ("recurrence", ctypes.c_int32), ("wave_split", ctypes.c_int32),
                 ("obs_read", ctypes.c_int32), ("seed_trig", ctypes.c_int32),
-                ("order", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+                ("order", ctypes.c_int32), ("kernels", ctypes.c_int32)]
+
+
+class MatrixShape(ctypes.Structure):
+    _fields_ = [("wave_bins", ctypes.c_int64), ("n_items", ctypes.c_int64),
+                ("waves", ctypes.c_int32), ("shared", ctypes.c_int32), ("parts", ctypes.c_int32),
+                ("reserved", ctypes.c_int32)]
 
 
 class FeatureOptions(ctypes.Structure):
@@ -214,6 +221,9 @@ def lib():
                                           ctypes.POINTER(ctypes.c_int64),
                                           ctypes.POINTER(ctypes.c_int64),
                                           ctypes.POINTER(ctypes.c_int64)]
+        L.lsp_describe_matrix.restype = ctypes.c_int
+        L.lsp_describe_matrix.argtypes = [i64, i64, ctypes.POINTER(Grid), ctypes.POINTER(Options),
+                                          i32, ctypes.POINTER(MatrixShape)]
         L.lsp_row_order_workspace_bytes.restype = sz
         L.lsp_row_order_workspace_bytes.argtypes = []
         L.lsp_row_order.restype = ctypes.c_int
@@ -244,8 +254,11 @@ def set_stage_events(begin, end):
 def describe_launch(n_obj, n_obs, grid, opt, generalized=False):
     """The launch shape a whole-grid call resolves (lsp_describe_launch):
     a dict with the resolved k_per_lane, waves_per_wg, t_split, schedule,
-    recurrence, wave_split, obs_read, seed_trig, tile_freqs, tiles_per_item and
-    n_items."""
+    recurrence, wave_split, obs_read, seed_trig, kernels, tile_freqs,
+    tiles_per_item and n_items, and, under "matrix", the shape of the matrix-core
+    kernels (lsp_describe_matrix) where the call runs those (kernels ==
+    KERNELS_MATRIX; the other entries are then what its vector kernels would
+    take), else None."""
     out = Options()
     tf, tpi, ni = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_int64(0)
     st = lib().lsp_describe_launch(int(n_obj), int(n_obs), ctypes.byref(grid), ctypes.byref(opt),
@@ -256,6 +269,15 @@ def describe_launch(n_obj, n_obs, grid, opt, generalized=False):
     d = {name: int(getattr(out, name)) for name, _ in Options._fields_}
     d["tile_freqs"], d["tiles_per_item"], d["n_items"] = int(tf.value), int(tpi.value), \
         int(ni.value)
+    d["matrix"] = None
+    if out.kernels == KERNELS_MATRIX:
+        m = MatrixShape()
+        st = lib().lsp_describe_matrix(int(n_obj), int(n_obs), ctypes.byref(grid),
+                                       ctypes.byref(opt), int(bool(generalized)), ctypes.byref(m))
+        if st != OK:
+            raise LspError(st, "lsp_describe_matrix")
+        d["matrix"] = {name: int(getattr(m, name)) for name, _ in m._fields_
+                       if name != "reserved"}
     return d
 
 
@@ -298,7 +320,8 @@ def make_grid(f_min, f_max, n_f, unit=CYCLES):
 
 def make_options(form=FORM_FP64, normalize=True, subtract_mean=True, pgram_dtype=PGRAM_F32, k=0,
                  waves=0, t_split=0, schedule=SCHED_AUTO, recurrence=REC_AUTO,
-                 wave_split=WSPLIT_AUTO, obs_read=0, seed_trig=0, order=ORDER_AUTO):
+                 wave_split=WSPLIT_AUTO, obs_read=0, seed_trig=0, order=ORDER_AUTO,
+                 kernels=KERNELS_AUTO):
     o = Options()
     o.form, o.normalize, o.subtract_mean, o.pgram_dtype = (int(form), int(bool(normalize)),
                                                            int(bool(subtract_mean)),
@@ -310,6 +333,7 @@ def make_options(form=FORM_FP64, normalize=True, subtract_mean=True, pgram_dtype
     o.obs_read = int(obs_read)
     o.seed_trig = int(seed_trig)
     o.order = int(order)
+    o.kernels = int(kernels)
     return o
 
 
@@ -354,7 +378,7 @@ class Periodogram:
                  normalize=True, subtract_mean=True, pgram=True, pgram_dtype=PGRAM_F32,
                  peaks=True, k=0, waves=0, t_split=0, schedule=SCHED_AUTO,
                  recurrence=REC_AUTO, wave_split=WSPLIT_AUTO, method="standard", dy=None,
-                 obs_read=0, seed_trig=0, order=ORDER_AUTO):
+                 obs_read=0, seed_trig=0, order=ORDER_AUTO, kernels=KERNELS_AUTO):
         _check(t, torch.float64, "t")
         _check(y, torch.float64, "y")
         if t.numel() != y.numel():
@@ -376,7 +400,8 @@ class Periodogram:
         self.n_obj = 1 if offsets is None else int(offsets.numel()) - 1
         self.grid = make_grid(f_min, f_max, n_f, unit)
         self.opt = make_options(form, normalize, subtract_mean, pgram_dtype, k, waves, t_split,
-                                schedule, recurrence, wave_split, obs_read, seed_trig, order)
+                                schedule, recurrence, wave_split, obs_read, seed_trig, order,
+                                kernels)
         dev = t.device
         nb = (gen_workspace_bytes if self.gen else workspace_bytes)(self.n_obj, self.n_obs,
                                                                    self.grid, self.opt)
@@ -424,7 +449,8 @@ class Periodogram:
         return self
 
     def launch(self):
-        """The launch shape this call resolves (see describe_launch)."""
+        """The launch shape this call resolves, and the kernels it runs (see
+        describe_launch)."""
         return describe_launch(self.n_obj, self.n_obs, self.grid, self.opt, self.gen)
 
     def capture(self):
@@ -549,7 +575,7 @@ class Rows:
                  rows_per_group=1, unit=CYCLES, form=FORM_FP32P, normalize=True,
                  subtract_mean=True, pgram=None, pgram_dtype=PGRAM_F32, peaks=None, k=0,
                  waves=0, schedule=SCHED_AUTO, recurrence=REC_AUTO, max_rows=None,
-                 method="standard", dy=None, order=ORDER_AUTO):
+                 method="standard", dy=None, order=ORDER_AUTO, kernels=KERNELS_AUTO):
         for x, dt, nm in ((t, torch.float64, "t"), (y, torch.float64, "y"),
                           (offsets, torch.int64, "offsets")):
             _check(x, dt, nm)
@@ -572,7 +598,7 @@ class Rows:
         self.n_obj = int(offsets.numel()) - 1
         self.grid = make_grid(f_min, f_max, n_f, unit)
         self.opt = make_options(form, normalize, subtract_mean, pgram_dtype, k, waves, 0,
-                                schedule, recurrence, order=order)
+                                schedule, recurrence, order=order, kernels=kernels)
         self.band_bins = int(band_bins) if row_band is not None else 0
         self.rows_per_group = int(rows_per_group)
         named = row_obj if row_obj is not None else row_band
