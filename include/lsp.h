@@ -441,22 +441,24 @@ lsp_status lsp_plan_launch(lsp_plan plan, void *stream);
 void lsp_plan_destroy(lsp_plan plan);
 
 /*
- * Launch-shape autotuner for the FP32 form's vector kernels (the matrix-core
- * kernels, which run when every tuning field is 0, need no tuning and are the
- * faster choice on the sizes measured).  Times candidate shapes (K
- * frequencies per lane, wavefronts per workgroup, recurrence, schedule and,
- * for one object, the observation split) on the caller's data -- for a batch,
- * on a prefix of its objects holding about 1e11 evaluations -- and writes the
- * fastest candidate whose peaks agree with the FP64 form on those objects
- * (within one bin on >= 99.9% of them, |dP| <= 1e-3 at the peaks) to *tuned
- * (base's other fields are kept).  offsets == NULL tunes single-object mode.
+ * Launch-shape autotuner for the FP32 form.  Times candidate shapes of the
+ * vector kernels (K frequencies per lane, wavefronts per workgroup, recurrence,
+ * schedule and, for one object, the observation split) and the matrix-core
+ * kernels on the caller's data -- for a batch, on a prefix of its objects
+ * holding about 1e11 evaluations -- and writes the fastest shape whose peaks
+ * agree with the FP64 form on those objects (within one bin on >= 99.9% of
+ * them, |dP| <= 1e-3 at the peaks) to *tuned (base's other fields are kept),
+ * with kernels LSP_KERNELS_VECTOR, or LSP_KERNELS_MATRIX where those kernels
+ * are faster still.  offsets == NULL tunes single-object mode.
  *   peak_scratch : device, >= n_obj lsp_peak records (overwritten).
  *   workspace    : device, >= lsp_autotune_workspace_bytes(...) bytes; smaller
  *                  workspaces skip the candidates that do not fit.
  *   cache_path   : host string or NULL.  When given, a JSON-lines file keyed by
  *                  device architecture and the log2 classes of n_obj, mean N_t
  *                  and n_f: a cached entry is returned without timing, and new
- *                  results are appended.
+ *                  results are appended.  An entry that names no kernels, of a
+ *                  file written before there was a choice, is returned with
+ *                  LSP_KERNELS_MATRIX.
  *   repeats      : timed launches per candidate (>= 1).
  * Synchronous (it reads results back to the host); allocates no device
  * memory.  Errors as lsp_batch, LSP_EUNSUPPORTED if no candidate passes.

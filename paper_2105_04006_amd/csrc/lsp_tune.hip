@@ -6,8 +6,10 @@
 // data -- for a batch, on a prefix of its objects large enough to fill the
 // device many times over -- and keeps the fastest candidate whose peaks agree
 // with the FP64 form on the same objects (within one bin on >= 99.9% of
-// objects, |dP| <= 1e-3 at the peaks).  Results can be cached per shape class
-// in a JSON-lines file.  The call is synchronous and allocates no device
+// objects, |dP| <= 1e-3 at the peaks).  The shapes are those of the vector
+// kernels; the matrix-core kernels, which have none to choose, are timed beside
+// them, and where they are the faster ones `kernels` says so beside the best
+// shape.  Results can be cached per shape class in a JSON-lines file.  The call is synchronous and allocates no device
 // memory: it runs in the caller's workspace and peak scratch.
 #include <math.h>
 #include <stdint.h>
@@ -46,11 +48,14 @@ bool cache_lookup(const char* path, const std::string& key, lsp_options* o) {
     while (fgets(line, sizeof line, f)) {
         char k[256];
         int kk, w, rec, sched, split, wsp;
+        // (an entry without kernels is of the time before the matrix-core
+        // kernels, which are faster than its shape)
+        int kernels = LSP_KERNELS_MATRIX;
         if (sscanf(line,
                    "{\"key\": \"%255[^\"]\", \"k_per_lane\": %d, \"waves_per_wg\": %d, "
                    "\"recurrence\": %d, \"schedule\": %d, \"t_split\": %d, "
-                   "\"wave_split\": %d",
-                   k, &kk, &w, &rec, &sched, &split, &wsp) == 7 &&
+                   "\"wave_split\": %d, \"kernels\": %d",
+                   k, &kk, &w, &rec, &sched, &split, &wsp, &kernels) >= 7 &&
             key == k) {
             o->k_per_lane = kk;
             o->waves_per_wg = w;
@@ -58,6 +63,7 @@ bool cache_lookup(const char* path, const std::string& key, lsp_options* o) {
             o->schedule = sched;
             o->t_split = split;
             o->wave_split = wsp;
+            o->kernels = kernels;
             found = true;  // the last entry for a key wins
         }
     }
@@ -72,14 +78,21 @@ void cache_store(const char* path, const std::string& key, const lsp_options& o,
     if (!f) return;
     fprintf(f,
             "{\"key\": \"%s\", \"k_per_lane\": %d, \"waves_per_wg\": %d, \"recurrence\": %d, "
-            "\"schedule\": %d, \"t_split\": %d, \"wave_split\": %d, \"ms\": %.6f}\n",
+            "\"schedule\": %d, \"t_split\": %d, \"wave_split\": %d, \"kernels\": %d, "
+            "\"ms\": %.6f}\n",
             key.c_str(), o.k_per_lane, o.waves_per_wg, o.recurrence, o.schedule, o.t_split,
-            o.wave_split, ms);
+            o.wave_split, o.kernels, ms);
     fclose(f);
 }
 
+// The matrix-core kernels, first and last (the first of a search runs before the
+// clocks are up), and the vector kernels' shapes between.
 std::vector<lsp_options> candidates(const lsp_options& base, bool single) {
     std::vector<lsp_options> out;
+    lsp_options matrix = base;
+    matrix.form = LSP_FORM_FP32P;
+    matrix.kernels = LSP_KERNELS_MATRIX;
+    out.push_back(matrix);
     const int ks[] = {8, 10, 12, 16, 32};
     // (eight waves per workgroup exist only with the in-workgroup wave split,
     // which only a single object's search covers)
@@ -106,8 +119,10 @@ std::vector<lsp_options> candidates(const lsp_options& base, bool single) {
                             o.schedule = sc;
                             o.t_split = sp;
                             o.wave_split = wsp ? LSP_WSPLIT_ON : LSP_WSPLIT_OFF;
+                            o.kernels = LSP_KERNELS_VECTOR;
                             out.push_back(o);
                         }
+    out.push_back(matrix);
     return out;
 }
 
@@ -140,6 +155,7 @@ size_t lsp_autotune_workspace_bytes(int64_t n_obj, int64_t n_obs, const lsp_grid
     ref.k_per_lane = ref.waves_per_wg = ref.t_split = 0;
     ref.schedule = LSP_SCHED_AUTO;
     ref.recurrence = LSP_REC_AUTO;
+    ref.kernels = LSP_KERNELS_AUTO;
     need = lsp_workspace_bytes(n_obj, n_obs, grid, &ref);
     if (need == 0) return 0;
     for (const lsp_options& o : lsp::candidates(base, n_obj == 1))
@@ -189,6 +205,7 @@ lsp_status lsp_autotune(const int64_t* offsets, int64_t n_obj, int64_t n_obs, co
     ref_opt.k_per_lane = ref_opt.waves_per_wg = ref_opt.t_split = 0;
     ref_opt.schedule = LSP_SCHED_AUTO;
     ref_opt.recurrence = LSP_REC_AUTO;
+    ref_opt.kernels = LSP_KERNELS_AUTO;
     lsp_status st = single ? lsp_single(t, y, m_obs, grid, &ref_opt, nullptr, peak_scratch,
                                         workspace, workspace_bytes, stream)
                            : lsp_batch(offsets, m, m_obs, t, y, grid, &ref_opt, nullptr,
@@ -205,8 +222,9 @@ lsp_status lsp_autotune(const int64_t* offsets, int64_t n_obj, int64_t n_obs, co
         (void)hipEventDestroy(e0);
         return LSP_EHIP;
     }
-    double best_ms = 1e300;
-    bool any = false;
+    double best_ms = 1e300, matrix_ms = 1e300;
+    lsp_options best = base;  // the best shape of the vector kernels
+    best.form = LSP_FORM_FP32P;
     for (const lsp_options& o : lsp::candidates(base, single)) {
         const size_t need = lsp_workspace_bytes(m, m_obs, grid, &o);
         if (need == 0 || need > workspace_bytes) continue;
@@ -236,17 +254,20 @@ lsp_status lsp_autotune(const int64_t* offsets, int64_t n_obj, int64_t n_obs, co
             break;
         }
         const double per = (double)ms / repeats;
-        if (per < best_ms) {
+        if (o.kernels == LSP_KERNELS_MATRIX) {
+            matrix_ms = std::min(matrix_ms, per);
+        } else if (per < best_ms) {
             best_ms = per;
-            *tuned = o;
-            any = true;
+            best = o;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st != LSP_OK) return st;
-    if (!any) return LSP_EUNSUPPORTED;
-    lsp::cache_store(cache_path, key, *tuned, best_ms);
+    if (std::min(best_ms, matrix_ms) >= 1e300) return LSP_EUNSUPPORTED;
+    best.kernels = matrix_ms <= best_ms ? LSP_KERNELS_MATRIX : LSP_KERNELS_VECTOR;
+    *tuned = best;
+    lsp::cache_store(cache_path, key, *tuned, std::min(best_ms, matrix_ms));
     return LSP_OK;
 }
 

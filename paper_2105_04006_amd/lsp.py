@@ -692,7 +692,8 @@ class Features:
 def autotune(t, y, f_min, f_max, n_f, offsets=None, unit=CYCLES, normalize=True,
              subtract_mean=True, cache_path=None, repeats=3, stream=None):
     """Run lsp_autotune on device data; returns the tuned keyword options
-    (k, waves, recurrence, schedule, t_split, wave_split) for Periodogram(form=FORM_FP32P)."""
+    (k, waves, recurrence, schedule, t_split, wave_split, kernels) for
+    Periodogram(form=FORM_FP32P)."""
     _check(t, torch.float64, "t")
     _check(y, torch.float64, "y")
     if offsets is not None:
@@ -715,7 +716,8 @@ def autotune(t, y, f_min, f_max, n_f, offsets=None, unit=CYCLES, normalize=True,
     if st != OK:
         raise LspError(st, "lsp_autotune")
     return dict(k=tuned.k_per_lane, waves=tuned.waves_per_wg, recurrence=tuned.recurrence,
-                schedule=tuned.schedule, t_split=tuned.t_split, wave_split=tuned.wave_split)
+                schedule=tuned.schedule, t_split=tuned.t_split, wave_split=tuned.wave_split,
+                kernels=tuned.kernels)
 
 
 def batch_static(offsets, t, y, f_min, f_max, n_f, pgram=None, peaks=None, unit=CYCLES,
