@@ -514,6 +514,7 @@ lsp_status run(const int64_t* offsets, int64_t n_obj, int64_t n_obs, const doubl
     pp.meta = at<ObjMeta>(ws, L.meta);
     pp.dy = method.dy;
     pp.gen = method.gen;
+    pp.scales = c.mx != kMxOff || f32;  // (the FP32 forms' fix-up takes matrix sums too)
     // Group keys, flag bits and counters are cleared by the statistics kernel
     // (up to 16 words a thread; one long series with many rows has more), else
     // by one of their own.  (Never by a memset: captured graphs replay both.)

@@ -574,6 +574,7 @@ struct PrepParams {
     ObjMeta* meta;
     const double* dy = nullptr;  // generalized form: errors (NULL: unit errors)
     int32_t gen = 0;             // generalized form: weights and a floating mean
+    int32_t scales = 1;          // ObjMeta::exps (matrix-core factors) are wanted
     uint32_t* zero = nullptr;    // words of the scratch memory to clear, for the kernels after
     int64_t zero_words = 0;
 };

@@ -80,11 +80,15 @@ __device__ double block_max(double v, double* sh) {
     return out;
 }
 
-// Observations of a thread that are loaded together, and then taken in order: a
+// AHEAD observations of a thread are loaded together, and then taken in order: a
 // long series' two passes are chains of loads (4,096 points with errors: 12.1 ->
-// 9.4 us, without 8.2 -> 5.8).
+// 9.4 us, without 8.2 -> 5.8).  Objects of up to 2,048 points have no such turn, and
+// with 80 registers instead of 56 their workgroups do not all fit the chip at
+// once; after that, 2,000 one-wave workgroups of the main kernel were unevenly
+// placed (253 -> 344 us).
 constexpr int kAhead = 8;
 
+template <int AHEAD>
 __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) {
     __shared__ Red sh_red[kPrepThreads / kWave];
     __shared__ double sh_sum[kPrepThreads / kWave];
@@ -127,16 +131,16 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
     };
     const bool errors = P.gen && P.dy;
     int64_t j = j0 + tid;
-    for (; j + (kAhead - 1) * kPrepThreads < j1; j += kAhead * kPrepThreads) {
-        double tj[kAhead], yj[kAhead], e[kAhead];
+    for (; AHEAD > 1 && j + (AHEAD - 1) * kPrepThreads < j1; j += AHEAD * kPrepThreads) {
+        double tj[AHEAD], yj[AHEAD], e[AHEAD];
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) {
+        for (int q = 0; q < AHEAD; ++q) {
             tj[q] = P.t[j + q * kPrepThreads];
             yj[q] = P.y[j + q * kPrepThreads];
             e[q] = errors ? P.dy[j + q * kPrepThreads] : 0.0;
         }
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) first(tj[q], yj[q], e[q]);
+        for (int q = 0; q < AHEAD; ++q) first(tj[q], yj[q], e[q]);
     }
     for (; j < j1; j += kPrepThreads) first(P.t[j], P.y[j], errors ? P.dy[j] : 0.0);
     r = block_reduce(r, sh_red);
@@ -157,21 +161,23 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const PrepParams P) 
         big_w = fmax(big_w, w);
     };
     j = j0 + tid;
-    for (; j + (kAhead - 1) * kPrepThreads < j1; j += kAhead * kPrepThreads) {
-        double yj[kAhead], w[kAhead];
+    for (; AHEAD > 1 && j + (AHEAD - 1) * kPrepThreads < j1; j += AHEAD * kPrepThreads) {
+        double yj[AHEAD], w[AHEAD];
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) {
+        for (int q = 0; q < AHEAD; ++q) {
             yj[q] = P.y[j + q * kPrepThreads];
             w[q] = P.gen ? gen_weight(P.dy, j + q * kPrepThreads, wnorm) : 1.0;
         }
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) second(yj[q], w[q]);
+        for (int q = 0; q < AHEAD; ++q) second(yj[q], w[q]);
     }
     for (; j < j1; j += kPrepThreads)
         second(P.y[j], P.gen ? gen_weight(P.dy, j, wnorm) : 1.0);
     const double syy = block_sum(sq, sh_sum);
-    big = block_max(big, sh_sum);
-    if (P.gen) big_w = block_max(big_w, sh_sum);
+    if (P.scales) {
+        big = block_max(big, sh_sum);
+        if (P.gen) big_w = block_max(big_w, sh_sum);
+    }
 
     if (tid == 0) {
         ObjMeta m = {};
@@ -247,7 +253,10 @@ hipError_t launch_stage(const ObjMeta* meta, const double* t, const double* y, i
 
 hipError_t launch_prep(const PrepParams& p, hipStream_t s) {
     if (p.n_obj <= 0) return hipSuccess;
-    hipLaunchKernelGGL(prep_kernel, grid_for(p.n_obj), dim3(kPrepThreads), 0, s, p);
+    if (p.n_obs >= p.n_obj * kAhead * kPrepThreads)  // 2,048 points on average
+        hipLaunchKernelGGL(prep_kernel<kAhead>, grid_for(p.n_obj), dim3(kPrepThreads), 0, s, p);
+    else
+        hipLaunchKernelGGL(prep_kernel<1>, grid_for(p.n_obj), dim3(kPrepThreads), 0, s, p);
     return hipGetLastError();
 }
 

@@ -53,7 +53,8 @@ def check(dev, method, series, lo, hi, n_f, what):
     for o in range(len(series)):
         assert gk["power"][o] == got[o, gk["index"][o]] == got[o].max()
     if method == "standard":
-        k2 = {id(a): np.minimum(shifted_condition(a, lo, hi, n_f) ** 2, 1e12) for a, _ in series}
+        times = {id(a): a for a, _ in series}  # (copies share theirs)
+        k2 = {i: np.minimum(shifted_condition(a, lo, hi, n_f) ** 2, 1e12) for i, a in times.items()}
         k2 = np.stack([k2[id(a)] for a, _ in series])
         near(got, ref, what, k2)
         return
