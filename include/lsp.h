@@ -64,9 +64,11 @@ enum {
     LSP_FORM_FP32P = 1  /* FP32 sums and trig, phases reduced in FP64, hardware
                            sin/cos, the bins reached from them by angle addition:
                            on the matrix cores (each factor as two f16 halves, 22
-                           significant bits, FP32 accumulators) where the library
-                           chooses the launch, else along a lane's frequencies on
-                           the vector units; ill-conditioned bins recomputed in FP64   */
+                           significant bits, FP32 accumulators; magnitudes and
+                           weights below 2^-13 of an object's largest keep fewer, in
+                           proportion) where the library chooses the launch, else
+                           along a lane's frequencies on the vector units;
+                           ill-conditioned bins recomputed in FP64                     */
 };
 
 /* Frequency unit of the grid. */
@@ -243,6 +245,10 @@ lsp_status lsp_single(const double *t, const double *y, int64_t n_t, const lsp_g
  *               peaks-only variant).
  *   peaks     : device, n_obj lsp_peak records, or NULL.
  *   workspace : device, >= lsp_workspace_bytes(n_obj, n_obs, grid, opt) bytes.
+ * The matrix-core kernels add an object's sums in an order that goes by the size
+ * of the call (n_obj, n_f, and n_obs for one series), so the last bits of its
+ * powers may differ between calls of different sizes; the same call gives the
+ * same bits.
  * Errors as lsp_single, plus LSP_EINVAL for NULL offsets or n_obj < 1, and
  * LSP_EUNSUPPORTED for t_split > 1 with n_obj > 1.
  */

@@ -49,7 +49,7 @@ struct Config {
     int64_t rec_room;       // records per group that the workspace has room for
     size_t spare;           // bytes that the workspace has on top
     int64_t n_obs;
-    bool keys;              // FP32 form, unsplit: per-group peak keys + tile flag bits
+    bool keys;              // FP32 form, split == 1: per-group peak keys + tile flag bits
     bool lpt;               // rows handed out longest first (lsp_order.hip)
     int mx;                 // matrix-core sums: kMxOff, kMxTiles or kMxSplit
     int mx_waves;           // kMxTiles: waves (2,048-bin tiles) per workgroup
@@ -342,7 +342,8 @@ int mx_series_parts(int64_t tiles, int64_t n_obs) {
 
 // The launch configuration of a call: the vector kernels' shape, or, where
 // every tuning field is left to the library, the matrix-core kernels'
-// (lsp_mx.hip with 1,024-bin fix-up tiles; lsp_fx.hip with 512-bin records).
+// (lsp_mx.hip with fix-up tiles of 1,024 bins, generalized 512; lsp_fx.hip with
+// 512-bin records).
 lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_options* given,
                    const Rows& rows, Config* c, const Method& method = Method{}) {
     lsp_options untuned;
@@ -368,9 +369,11 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     // points) 22 / 26; 1,000 tiles of 200 points 39 / 49, of 1,000 points
     // 108 / 93; one series of 4,096 points, 1,954 tiles, 463 / 575.  FP64: 400
     // tiles of 500 points 77 / 61, of 60 points 26 / 31; 782 tiles of one series
-    // of 2,000 points 251 / 267; 800 tiles of 300 points 55 / 62.  The
-    // count is that of the whole batch, so that parts of it (row mode, the
-    // host-return chunks) add their sums in the same order.
+    // of 2,000 points 251 / 267; 800 tiles of 300 points 55 / 62.  The line also
+    // depends on the points, as these show; it goes by the tiles alone, between
+    // them.  The count is that of the whole batch, so that parts of it (row mode,
+    // the host-return chunks) add their sums in the same order; the same object
+    // alone, in a small batch and in a large one may differ in the last bits.
     const int64_t wave_bins = f32 ? mx_item_bins(1, false, method.gen) : kFxTile;
     const int64_t count = rows.n_batch * rows.rows_per_group * ((n_f + wave_bins - 1) / wave_bins);
     const bool split = count <= (!f32 ? 512 : rows.n_batch > 1 ? 400 : 1024);

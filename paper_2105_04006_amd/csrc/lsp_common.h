@@ -55,7 +55,8 @@ constexpr int kFxTile = 512;
 // The matrix-core kernels scale an object's centred magnitudes by 2^e with
 // max |y - ybar| 2^e in [2^13, 2^14): the products with cosines stay below
 // f16's largest value, and the low half of a value's split stays a normal f16
-// down to 2^-13 of the largest magnitude.  The generalized form scales w and
+// down to 2^-13 of the largest magnitude.  (What is smaller keeps fewer bits, in
+// proportion; every sum holds the largest too.)  The generalized form scales w and
 // w (y - ybar) the same way, each by its own power.
 __device__ __forceinline__ int mx_scale_exp(double largest) {
     if (!(largest > 0.0) || !isfinite(largest)) return 0;
@@ -370,8 +371,8 @@ __device__ __forceinline__ void seed_sincos(float r, float* s, float* c) {
     }
 }
 
-// One observation's contribution to a lane's K bins (the FP32 hot loop of the
-// periodogram and of the coarse proposal features): seed (cos, sin) of the
+// One observation's contribution to a lane's K bins (the hot loop of the FP32
+// form's vector kernels): seed (cos, sin) of the
 // lane's first phase, then the recurrence across its bins.  o = (y - ybar,
 // cos step, sin step, -), tq = t - t0.
 template <int K, bool CHEB, int TRIG>
@@ -596,14 +597,16 @@ struct MainParams {
     int64_t tiles_per_item; // consecutive frequency tiles per work item (FP32 form)
     int64_t chunks_per_row; // ceil(tiles_per_row / tiles_per_item)
     int64_t n_items;        // n_rows * chunks_per_row * n_split
-    int32_t n_split;        // observation-axis split (single object only)
+    int32_t n_split;        // observation-axis split (single object only): of the vector
+                            // kernels, or parts of the matrix-core ones
     int32_t pgram_f64;
     void* pgram;             // NULL: peaks only
     PeakRec* rec;            // FP64 form: [n_rows * tiles_per_row] tile records
-    unsigned long long* keys;  // FP32 form, n_split == 1: [n_groups] peak keys (peak_key)
-    uint32_t* ill_bits;      // FP32 form, n_split == 1: bit per tile, set when the tile
+    unsigned long long* keys;  // FP32 form, no split of the vector kernels: [n_groups]
+                               // peak keys (peak_key)
+    uint32_t* ill_bits;      // with keys: bit per tile, set when the tile
                              // needs the FP64 fix-up (its key then comes from the fix-up)
-    float* part;             // [n_split][4][n_f] when n_split > 1
+    float* part;             // [n_split][4, generalized 6][n_f] when n_split > 1
     unsigned int* queue;     // persistent schedule: kXcds counters
     const int32_t* row_perm = nullptr;  // rank -> row (longest first); NULL: rank = row
     // with row_perm: the number of rows with work (they hold the first ranks
@@ -687,12 +690,13 @@ hipError_t launch_stage(const ObjMeta* meta, const double* t, const double* y, i
 hipError_t launch_gen_fp32p(const MainParams& p, int k, int waves, hipStream_t s);
 // Matrix-core sums (lsp_mx.hip): `waves` (1, 2 or 4; 4 for the generalized form)
 // tiles of 2,048 (generalized 1,024) bins per workgroup, or, with `split`, one
-// tile whose observations the waves share.
+// tile whose observations the waves share, and P.n_split workgroups where a long
+// series is split further.
 int64_t mx_item_bins(int waves, bool split, bool gen);
 hipError_t launch_mx(const MainParams& p, int waves, bool split, hipStream_t s);
 hipError_t launch_gen_fp64(const MainParams& p, int kf, int waves, hipStream_t s);
 // FP64 sums on the matrix cores (lsp_fx.hip): four 512-bin tiles per workgroup,
-// or, with `split`, one tile whose observations 4 or 8 waves share.
+// or, with `split`, one tile whose observations eight waves share.
 int64_t fx_item_bins(int waves, bool split);
 hipError_t launch_fx(const MainParams& p, int waves, bool split, hipStream_t s);
 // k: the call's peaks where the fix-up writes them (fixup_writes_peaks), else

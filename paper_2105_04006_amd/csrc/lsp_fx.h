@@ -29,7 +29,7 @@
 // points on 10,000 bins 82 -> 23 us; the FP64 recompute of 300 asteroid-like
 // objects 1370 -> 78 us.  (The residual's second halves cost the first 2 %.)
 // Error against an extended-precision evaluation (2-norm of a tile, ten years, 60
-// and 1,000 points): 2.4e-16 and 4.5e-16 from 12 to 340 cycles a day, term by term
+// and 1,000 points; the same arithmetic on the host): 2.4e-16 and 4.5e-16 from 12 to 340 cycles a day, term by term
 // 2.1e-16 and 6.3e-16.
 //
 // A bin whose smaller denominator (N - R, or T - R) is at most N/256 loses more

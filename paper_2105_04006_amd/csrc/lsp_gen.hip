@@ -19,7 +19,7 @@
 //   sum w' cos^2 = sum u u,  sum w' cos sin = sum u v,
 // plus two for the recurrence: 8 instructions per evaluation against the
 // standard form's 6.  Bins whose smaller denominator is below N/32 mark their
-// tile for the FP64 fix-up, which recomputes it with power64_gen_bin.
+// tile for the FP64 fix-up (lsp_fx.hip).
 //
 // FP64 form: a library sincos per term, as the standard FP64 form.
 #include "lsp_common.h"

@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kWave* kSplitW, 2) void mx_split_kernel(const MainP
 // would leave one wave per SIMD, so a wave's tile is 16 blocks x 32 offsets
 // (1,024 bins, two fix-up tiles) on v_mfma_f32_16x16x32_f16: 72 matrix
 // instructions per 32 observations.  Measured, vector kernels -> here: 4,096
-// points with errors on 500,000 bins 422 -> 124 us; error 1.1e-6 -> 2.3e-7.
+// points with errors on 500,000 bins 413 -> 112 us; error 1.1e-6 -> 2.3e-7.
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kGSlice = 32;                  // observations per matrix instruction
