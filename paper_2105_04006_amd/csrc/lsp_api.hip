@@ -47,6 +47,7 @@ struct Config {
     int64_t n_items;
     int64_t rec_per_group;  // records per group (tile records or combine blocks)
     int64_t rec_room;       // records per group that the workspace has room for
+    int part_room;          // floats per bin that the workspace has for partial sums
     size_t spare;           // bytes that the workspace has on top
     int64_t n_obs;
     bool keys;              // FP32 form, split == 1: per-group peak keys + tile flag bits
@@ -282,6 +283,7 @@ lsp_status resolve_vector(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const
     c->rec_per_group = c->split > 1 ? (n_f + kCombineThreads - 1) / kCombineThreads
                                     : c->tiles_per_row * rows.rows_per_group;
     c->rec_room = c->rec_per_group;
+    c->part_room = c->split > 1 ? c->split * (c->gen ? 6 : 4) : 0;
     c->spare = 0;
     // The FP32 forms merge each group's peak into one 64-bit key whose index
     // field holds 32 bits (peak_key).
@@ -391,15 +393,22 @@ lsp_status resolve(int64_t n_obj, int64_t n_obs, const lsp_grid* g, const lsp_op
     // (room for either kernel's records: which one runs depends on n_obs, and the
     // workspace must not)
     c->rec_room = std::max(c->rec_room, tiles * rows.rows_per_group);
+    c->part_room = 0;
     // a program may size one buffer for both methods from the generalized
     // call, which has always asked for more than the standard one: keep it so
+    // (and see the parts below)
     c->spare = method.gen ? kAlign : 0;
     if (!f32 && (double)n_obs <= (double)rows.n_batch * fp64_vector_points(n_f, split, method.gen))
         return LSP_OK;
     c->mx = split ? kMxSplit : kMxTiles;
     c->mx_waves = waves;
-    if (f32 && split && rows.whole && n_obj == 1)
+    if (f32 && split && rows.whole && n_obj == 1) {
+        auto floats = [](int parts, int sums) { return parts > 1 ? parts * sums : 0; };
         c->mx_parts = mx_series_parts((n_f + bins - 1) / bins, n_obs);
+        const int64_t wide = mx_item_bins(1, true, false);
+        c->part_room = std::max(floats(c->mx_parts, method.gen ? 6 : 4),
+                                floats(mx_series_parts((n_f + wide - 1) / wide, n_obs), 4));
+    }
     c->split = 1;
     c->persistent = 0;
     c->tile_freqs = tile;
@@ -432,8 +441,7 @@ Layout layout(int64_t n_obj, const lsp_grid* g, const Rows& rows, const Config& 
     L.zero_words = c.keys ? (off - L.keys) / 4 : 0;
     off = align_up(off);
     L.part = off;
-    const size_t parts = (size_t)(c.split > 1 ? c.split : c.mx_parts);
-    off += parts > 1 ? align_up(parts * (c.gen ? 6 : 4) * (size_t)g->n_f * sizeof(float)) : 0;
+    off += align_up((size_t)c.part_room * (size_t)g->n_f * sizeof(float));
     // LSP_OBS_DIRECT: per-observation staged values (indexed like t)
     const size_t n_obs = c.obs == LSP_OBS_DIRECT ? (size_t)c.n_obs : 0;
     L.stage_t = off;

@@ -63,3 +63,15 @@ def test_kernels_field_takes_the_reserved_one():
     for v in (-1, 3, 77):
         opt.kernels = v
         assert lsp.describe_launch(1, 256, g, opt) == want
+
+
+@pytest.mark.parametrize("form", [lsp.FORM_FP32P, lsp.FORM_FP64])
+def test_generalized_workspace_serves_the_standard_form(form):
+    """A program may size one buffer for both methods from the generalized call."""
+    opt = lsp.make_options(form=form)
+    for n_obj in (1, 2, 40, 3000):
+        for n_f in (1, 500, 2000, 10_000, 60_000, 130_000, 500_000, 3_000_000):
+            for n in (1, 30, 600, 1500, 5000, 20_000, 1_000_000):
+                g = lsp.make_grid(0.5, 24.0, n_f)
+                std = lsp.workspace_bytes(n_obj, n_obj * n, g, opt)
+                assert 0 < std <= lsp.gen_workspace_bytes(n_obj, n_obj * n, g, opt), (n_obj, n_f, n)
